@@ -129,7 +129,7 @@ def _step_work(s):
 
 # Sources whose code a step's dominant kernel is built from.
 KERNEL_SOURCES = {
-    "gemm": ["gemm.hip", "common.h", "kernels.h"],
+    "gemm": ["gemm.hip", "gemm_common.h", "common.h", "kernels.h"],
     "attn": ["attn.hip", "common.h", "kernels.h"],
     "ln": ["ln.hip", "common.h", "kernels.h"],
     "lamb": ["lamb.hip", "common.h", "kernels.h"],

@@ -22,72 +22,16 @@
 // G, out-projection bias + residual, and the GeLU derivative in the backward
 // pass.
 //
-// fp32 path: a plain LDS-tiled SIMT kernel with the same epilogues.
+// The fp32 GEMMs, with the same epilogues, are in gemm_f32.hip.
 #include <algorithm>
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_common.h"
 #include "kernels.h"
 
 namespace pb {
 namespace {
-
-// ------------------------------------------------------------- epilogues
-// Four consecutive output columns n..n+3 of row m.  GT: tanh form of GeLU.
-template <typename T, Epi EPI, bool GT>
-PB_DEV void epi_store4(const EpiArgs& ep, int m, int n, const float* v) {
-  if constexpr (EPI == Epi::StoreF32) {
-    store4((float*)ep.out + (size_t)m * ep.ld_out + n, v);
-  } else if constexpr (EPI == Epi::LnGrad) {
-    store4((T*)ep.out + (size_t)m * ep.ld_out + n, v);
-  } else if constexpr (EPI == Epi::BiasGelu) {
-    float b[4], z[4];
-    load4((const T*)ep.bias + n, b);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) z[e] = v[e] + b[e];
-    store4((T*)ep.out + (size_t)m * ep.ld_out + n, z);
-    if (n >= ep.split) {
-      float g[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) g[e] = gelu<GT>(z[e]);
-      store4((T*)ep.out2 + (size_t)m * ep.ld_out2 + (n - ep.split) + ep.col2, g);
-    }
-  } else if constexpr (EPI == Epi::BiasResid) {
-    float b[4], r[4], o[4];
-    load4((const T*)ep.bias + n, b);
-    load4((const T*)ep.resid + (size_t)m * ep.ld_out + n, r);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = v[e] + b[e] + r[e];
-    store4((T*)ep.out + (size_t)m * ep.ld_out + n, o);
-  } else {  // DgeluSplit
-    if (n < ep.split) {
-      store4((T*)ep.out + (size_t)m * ep.ld_out + n, v);
-    } else {
-      const size_t off = (size_t)m * ep.ld_out2 + (n - ep.split) + ep.col2;
-      float u[4], o[4];
-      load4((const T*)ep.aux + off, u);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = v[e] * gelu_grad<GT>(u[e]);
-      store4((T*)ep.out2 + off, o);
-    }
-  }
-}
-
-// LnGrad: the LayerNorm backward's row terms of four columns n..n+3 of row m,
-// added to s1 (sum g) and s2 (sum g xhat), g = gamma dh.
-template <typename T>
-PB_DEV void ln_terms4(const EpiArgs& ep, int m, int n, const float* v, float mu, float rs,
-                      float& s1, float& s2) {
-  float gm[4], xv[4];
-  load4((const T*)ep.bias + n, gm);
-  load4((const T*)ep.aux + (size_t)m * ep.ld_out + n, xv);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float g = gm[e] * v[e];
-    s1 += g;
-    s2 += g * ((xv[e] - mu) * rs);
-  }
-}
 
 // --------------------------------------------------------- bf16 MFMA GEMM
 // 256 x 256 output tile, K-tile 64, eight waves in a 4 (m) x 2 (n) grid, each
@@ -99,37 +43,8 @@ constexpr int kThreads = 64 * kWavesM * kWavesN;
 constexpr int kWTM = kBM / kWavesM, kWTN = kBN / kWavesN;
 constexpr int kTM = kWTM / 32, kTN = kWTN / 32;
 constexpr int kTileBytes = kBM * kBK * 2;  // one operand tile (32 KB)
-// CUs of MI355X; the DMA kernels' 128 KB of LDS allows one workgroup per CU.
-constexpr int kCUs = 256;
-
 // 16-byte chunk c (0..7) of LDS row `row` lives at physical chunk swz(row, c).
 PB_DEV int swz(int row, int c) { return c ^ ((row ^ (row >> 3)) & 7); }
-
-// Tile order.  Workgroup b runs on XCD b % 8; xcd_remap gives each XCD a
-// contiguous run of logical ids, and tile_of walks logical ids in groups of G
-// tile-rows, so concurrently running workgroups on one XCD share operand
-// strips in its L2.  The LDS-DMA GEMMs take G = tile_group(epilogue): groups
-// of 4 rows (a 32-workgroup XCD share spans 4 x 8 tiles) measured faster for
-// the backward's GEMMs and the in-projection, groups of 8 for the
-// out-projection (BiasResid); groups of 2 or 16 were slower for all.
-PB_DEV int xcd_remap(int bid, int n) {
-  const int q = n / 8, r = n % 8, x = bid % 8;
-  return x * q + min(x, r) + bid / 8;
-}
-constexpr int tile_group(Epi e) { return e == Epi::BiasResid ? 8 : 4; }
-template <int G = 8>
-PB_DEV void tile_of(int lid, int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int per_group = G * tiles_n;
-  const int group = lid / per_group;
-  const int first_m = group * G;
-  const int gsize = min(tiles_m - first_m, G);
-  const int in_group = lid - group * per_group;
-  tm = first_m + in_group % gsize;
-  tn = in_group / gsize;
-}
-PB_DEV void tile_coords(int tiles_m, int tiles_n, int& tm, int& tn) {
-  tile_of(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
-}
 
 // Epilogue of one wave's 64 x 128 block of a 256 x 256 tile.  acc[i][j][4 jj +
 // e] is C(m, n) with m = mw + 32 i + (lane & 31), n = nw + 32 j + 8 jj +
@@ -1075,65 +990,6 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float* __restrict__ p
   }
 }
 
-// ----------------------------------------------------------- fp32 SIMT GEMM
-constexpr int kSB = 64, kSK = 16;
-
-template <bool AK, bool BK, Epi EPI, bool GT>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda,
-                                                       const float* __restrict__ B, int ldb,
-                                                       int M, int N, int K, EpiArgs ep) {
-  __shared__ float as[kSK][kSB + 4];
-  __shared__ float bs[kSK][kSB + 4];
-  const int m0 = blockIdx.y * kSB, n0 = blockIdx.x * kSB;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += kSK) {
-    for (int e = threadIdx.x; e < kSB * kSK; e += 256) {
-      const int r = e / kSK, kk = e % kSK;  // r: m or n within the tile
-      const int k = k0 + kk;
-      const int m = m0 + r, n = n0 + r;
-      float av = 0.f, bv = 0.f;
-      if (k < K && m < M) av = AK ? A[(size_t)m * lda + k] : A[(size_t)k * lda + m];
-      if (k < K && n < N) bv = BK ? B[(size_t)n * ldb + k] : B[(size_t)k * ldb + n];
-      as[kk][r] = av;
-      bs[kk][r] = bv;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < kSK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = as[kk][ty * 4 + i];
-        b[i] = bs[kk][tx * 4 + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i, n = n0 + tx * 4;
-    const bool ok = m < M && n < N;
-    if (ok) epi_store4<float, EPI, GT>(ep, m, n, acc[i]);
-    if constexpr (EPI == Epi::LnGrad) {
-      // the 16 lanes tx = 0..15 of a row cover its 64-column group n0 .. n0 + 63
-      float s1 = 0.f, s2 = 0.f;
-      if (ok) ln_terms4<float>(ep, m, n, acc[i], ep.mean[m], ep.rstd[m], s1, s2);
-#pragma unroll
-      for (int off = 8; off > 0; off >>= 1) {
-        s1 += __shfl_xor(s1, off, 16);
-        s2 += __shfl_xor(s2, off, 16);
-      }
-      if (tx == 0 && m < M && n0 < N)
-        ep.rowpart[(size_t)m * ep.rowpart_ld + n0 / 64] = make_float2(s1, s2);
-    }
-  }
-}
-
 // The DMA path addresses a tile as scalar base + 32-bit lane offset.
 bool dma_offsets_fit(bool ak, int lda, bool bk, int ldb) {
   auto fits = [](bool kc, int ld) {
@@ -1152,7 +1008,7 @@ void gemm_dispatch_layout(Dt dt, const void* A, int lda, const void* B, int ldb,
     static_assert(kStages * 2 * kDTile == 4 * kTileBytes, "DMA path LDS");
     if (K % kBK == 0 && dma_offsets_fit(AK, lda, BK, ldb)) {
       SplitPlan sp = gemm_split_plan(dt, M, N, K);
-      if (sp.tail > 0 && (!split_ws || split_ws_floats < gemm_split_floats(sp)))
+      if (sp.tail > 0 && (!split_ws || split_ws_floats < gemm_split_floats(dt, M, N, K)))
         sp = SplitPlan{tiles, 0, 1};
       gemm_bf16_dma_kernel<AK, BK, EPI, GT><<<sp.n_full + sp.tail * sp.splits, kThreads, lds, s>>>(
           (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, ep, sp.n_full, sp.splits, split_ws);
@@ -1162,9 +1018,8 @@ void gemm_dispatch_layout(Dt dt, const void* A, int lda, const void* B, int ldb,
       gemm_bf16_kernel<AK, BK, EPI, GT><<<tiles, kThreads, lds, s>>>(
           (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, ep);
   } else {
-    dim3 grid((N + kSB - 1) / kSB, (M + kSB - 1) / kSB);
-    gemm_f32_kernel<AK, BK, EPI, GT><<<grid, 256, 0, s>>>((const float*)A, lda, (const float*)B,
-                                                          ldb, M, N, K, ep);
+    launch_gemm_f32(EPI, AK, BK, (const float*)A, lda, (const float*)B, ldb, M, N, K, ep,
+                    split_ws, split_ws_floats, s);
   }
 }
 
@@ -1209,7 +1064,9 @@ SplitPlan gemm_split_plan(Dt dt, int M, int N, int K) {
   return SplitPlan{0, tiles, best};
 }
 
-size_t gemm_split_floats(const SplitPlan& p) {
+size_t gemm_split_floats(Dt dt, int M, int N, int K) {
+  const SplitPlan p = dt == Dt::F32 ? gemm_f32_launch_of(M, N, K).plan
+                                    : gemm_split_plan(dt, M, N, K);
   return (size_t)p.tail * p.splits * kBM * kBN;
 }
 
@@ -1221,10 +1078,7 @@ GemmLaunch gemm_launch_of(Dt dt, int M, int N, int K) {
     g.workgroups = g.plan.n_full + g.plan.tail * g.plan.splits;
     g.threads = kThreads;
   } else {
-    g.tiles = ((M + kSB - 1) / kSB) * ((N + kSB - 1) / kSB);
-    g.plan = SplitPlan{g.tiles, 0, 1};
-    g.workgroups = g.tiles;
-    g.threads = 256;
+    g = gemm_f32_launch_of(M, N, K);
   }
   return g;
 }

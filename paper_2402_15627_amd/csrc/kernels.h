@@ -140,7 +140,8 @@ struct SplitPlan {
   int n_full, tail, splits;
 };
 SplitPlan gemm_split_plan(Dt dt, int M, int N, int K);
-size_t gemm_split_floats(const SplitPlan& p);
+// Floats of partial results that the GEMM's split launch needs (0: unsplit).
+size_t gemm_split_floats(Dt dt, int M, int N, int K);
 // The launch of one GEMM given a full split workspace, as launch_gemm makes
 // it for operands whose LDS-DMA offsets fit 32 bits: output tiles, the tail
 // split, and the main kernel's grid.
@@ -150,6 +151,12 @@ struct GemmLaunch {
   int workgroups, threads;
 };
 GemmLaunch gemm_launch_of(Dt dt, int M, int N, int K);
+// The fp32 GEMMs (gemm_f32.hip): tiles of 64 x 64 (whole, or every tile split
+// along K, its slices' partial results summed by a second kernel) or 16 x 64.
+GemmLaunch gemm_f32_launch_of(int M, int N, int K);
+void launch_gemm_f32(Epi epi, bool a_kcontig, bool b_kcontig, const float* A, int lda,
+                     const float* B, int ldb, int M, int N, int K, const EpiArgs& ep, float* ws,
+                     size_t ws_floats, hipStream_t s);
 // split_ws may be NULL (or too small): the GEMM then runs unsplit.
 void launch_gemm(Dt dt, Epi epi, bool a_kcontig, bool b_kcontig, const void* A, int lda,
                  const void* B, int ldb, int M, int N, int K, const EpiArgs& ep, float* split_ws,

@@ -133,17 +133,17 @@ SavedLayout saved_layout(const Dims& d) {
 // so one region serves both.
 size_t split_bytes_fwd(const Dims& d, pb::Dt dt) {
   const int T = (int)d.T, H = (int)d.H, N_in = (int)d.N_in, K_out = (int)d.K_out;
-  size_t m = std::max(pb::gemm_split_floats(pb::gemm_split_plan(dt, T, N_in, H)),
-                      pb::gemm_split_floats(pb::gemm_split_plan(dt, T, H, K_out))) * 4;
+  size_t m = std::max(pb::gemm_split_floats(dt, T, N_in, H),
+                      pb::gemm_split_floats(dt, T, H, K_out)) * 4;
   const pb::AttnShape a = attn_shape(d);
   return std::max(m, pb::attn_fwd_partial_bytes(a, pb::attn_split_plan(dt, a)));
 }
 size_t split_bytes_bwd(const Dims& d, pb::Dt dt) {
   const int T = (int)d.T, H = (int)d.H, N_in = (int)d.N_in, K_out = (int)d.K_out;
-  size_t m = pb::gemm_split_floats(pb::gemm_split_plan(dt, T, K_out, H));
-  m = std::max(m, pb::gemm_split_floats(pb::gemm_split_plan(dt, H, K_out, T)));
-  m = std::max(m, pb::gemm_split_floats(pb::gemm_split_plan(dt, T, H, N_in)));
-  m = std::max(m, pb::gemm_split_floats(pb::gemm_split_plan(dt, N_in, H, T)));
+  size_t m = pb::gemm_split_floats(dt, T, K_out, H);
+  m = std::max(m, pb::gemm_split_floats(dt, H, K_out, T));
+  m = std::max(m, pb::gemm_split_floats(dt, T, H, N_in));
+  m = std::max(m, pb::gemm_split_floats(dt, N_in, H, T));
   const pb::AttnShape a = attn_shape(d);
   return std::max(m * 4, pb::attn_bwd_partial_bytes(a, pb::attn_bwd_split_plan(dt, a)));
 }
@@ -212,7 +212,7 @@ SerialLayout serial_layout(const Dims& d) {
 size_t max_split_bytes(pb::Dt dt, std::initializer_list<std::array<int, 3>> shapes) {
   size_t m = 0;
   for (const auto& s : shapes)
-    m = std::max(m, pb::gemm_split_floats(pb::gemm_split_plan(dt, s[0], s[1], s[2])) * 4);
+    m = std::max(m, pb::gemm_split_floats(dt, s[0], s[1], s[2]) * 4);
   return m;
 }
 size_t serial_split_fwd(const Dims& d, pb::Dt dt) {
@@ -1293,7 +1293,7 @@ namespace {
 size_t rows_split_bytes(pb::Dt dt, int rows, int N, int K, int per_launch) {
   size_t m = 0;
   for (int k = 1; k <= per_launch; ++k)
-    m = std::max(m, pb::gemm_split_floats(pb::gemm_split_plan(dt, rows * k, N, K)) * 4);
+    m = std::max(m, pb::gemm_split_floats(dt, rows * k, N, K) * 4);
   return align256(m);
 }
 bool tp_args_ok(const pb_config* cfg, int tp, int per_launch) {
