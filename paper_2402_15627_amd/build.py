@@ -31,6 +31,7 @@ FLAGS = [
 # registers avoids per-tile copies between the two register files.
 EXTRA = {
     "attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm", "-disable-lsr"],
+    "attn_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 
 

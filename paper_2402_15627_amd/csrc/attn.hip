@@ -20,7 +20,7 @@
 // The backward pass is split in two kernels so that no gradient needs atomic
 // accumulation: results are deterministic.
 //
-// fp32 kernels: one thread per query (or key), plain loops; parity path.
+// The fp32 kernels are in attn_f32.hip.
 #include <algorithm>
 #include <type_traits>
 
@@ -1129,112 +1129,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
                bx - nxk, wi.head, wi.b);
 }
 
-// ============================================================ fp32 path
-template <int D>
-__global__ __launch_bounds__(64) void attn_fwd_f32(const float* __restrict__ Q,
-                                                   const float* __restrict__ K,
-                                                   const float* __restrict__ V, int ld,
-                                                   float* __restrict__ O, int ld_o,
-                                                   float* __restrict__ lse, int S, int H, int W,
-                                                   float scale) {
-  const int q = blockIdx.x * 64 + threadIdx.x, head = blockIdx.y, b = blockIdx.z;
-  if (q >= S) return;
-  const size_t tok0 = (size_t)b * S;
-  const float* qr = Q + (tok0 + q) * ld + head * D;
-  float qv[D], acc[D];
-  for (int e = 0; e < D; ++e) { qv[e] = qr[e]; acc[e] = 0.f; }
-  float m = kNegInf, l = 0.f;
-  for (int j = max(0, q - W + 1); j <= q; ++j) {
-    const float* kr = K + (tok0 + j) * ld + head * D;
-    const float* vr = V + (tok0 + j) * ld + head * D;
-    float s = 0.f;
-    for (int e = 0; e < D; ++e) s = fmaf(qv[e], kr[e], s);
-    s *= scale;
-    const float mn = fmaxf(m, s);
-    const float a = expf(m - mn), p = expf(s - mn);
-    l = l * a + p;
-    for (int e = 0; e < D; ++e) acc[e] = acc[e] * a + p * vr[e];
-    m = mn;
-  }
-  float* orow = O + (tok0 + q) * ld_o + head * D;
-  for (int e = 0; e < D; ++e) orow[e] = acc[e] / l;
-  lse[((size_t)b * H + head) * S + q] = m + logf(l);
-}
-
-template <int D>
-__global__ __launch_bounds__(64) void attn_dq_f32(const float* __restrict__ Q,
-                                                  const float* __restrict__ K,
-                                                  const float* __restrict__ V, int ld,
-                                                  const float* __restrict__ dO, int ld_o,
-                                                  const float* __restrict__ lse,
-                                                  const float* __restrict__ delta,
-                                                  float* __restrict__ dQ, int ld_d, int S, int H,
-                                                  int W, float scale) {
-  const int q = blockIdx.x * 64 + threadIdx.x, head = blockIdx.y, b = blockIdx.z;
-  if (q >= S) return;
-  const size_t tok0 = (size_t)b * S;
-  const float* qr = Q + (tok0 + q) * ld + head * D;
-  const float* gr = dO + (tok0 + q) * ld_o + head * D;
-  float qv[D], gv[D], acc[D];
-  for (int e = 0; e < D; ++e) { qv[e] = qr[e]; gv[e] = gr[e]; acc[e] = 0.f; }
-  const size_t ro = ((size_t)b * H + head) * S + q;
-  const float L = lse[ro], Dq = delta[ro];
-  for (int j = max(0, q - W + 1); j <= q; ++j) {
-    const float* kr = K + (tok0 + j) * ld + head * D;
-    const float* vr = V + (tok0 + j) * ld + head * D;
-    float s = 0.f, dp = 0.f;
-    for (int e = 0; e < D; ++e) {
-      s = fmaf(qv[e], kr[e], s);
-      dp = fmaf(gv[e], vr[e], dp);
-    }
-    const float ds = expf(s * scale - L) * (dp - Dq);
-    for (int e = 0; e < D; ++e) acc[e] = fmaf(ds, kr[e], acc[e]);
-  }
-  float* out = dQ + (tok0 + q) * ld_d + head * D;
-  for (int e = 0; e < D; ++e) out[e] = acc[e] * scale;
-}
-
-template <int D>
-__global__ __launch_bounds__(64) void attn_dkdv_f32(const float* __restrict__ Q,
-                                                    const float* __restrict__ K,
-                                                    const float* __restrict__ V, int ld,
-                                                    const float* __restrict__ dO, int ld_o,
-                                                    const float* __restrict__ lse,
-                                                    const float* __restrict__ delta,
-                                                    float* __restrict__ dK, float* __restrict__ dV,
-                                                    int ld_d, int S, int H, int W, float scale) {
-  const int j = blockIdx.x * 64 + threadIdx.x, head = blockIdx.y, b = blockIdx.z;
-  if (j >= S) return;
-  const size_t tok0 = (size_t)b * S;
-  const float* kr = K + (tok0 + j) * ld + head * D;
-  const float* vr = V + (tok0 + j) * ld + head * D;
-  float kv[D], vv[D], dk[D], dv[D];
-  for (int e = 0; e < D; ++e) { kv[e] = kr[e]; vv[e] = vr[e]; dk[e] = 0.f; dv[e] = 0.f; }
-  const size_t ro = ((size_t)b * H + head) * S;
-  const int i_end = min(S - 1, j + W - 1);
-  for (int i = j; i <= i_end; ++i) {
-    const float* qr = Q + (tok0 + i) * ld + head * D;
-    const float* gr = dO + (tok0 + i) * ld_o + head * D;
-    float s = 0.f, dp = 0.f;
-    for (int e = 0; e < D; ++e) {
-      s = fmaf(qr[e], kv[e], s);
-      dp = fmaf(gr[e], vv[e], dp);
-    }
-    const float p = expf(s * scale - lse[ro + i]);
-    const float ds = p * (dp - delta[ro + i]);
-    for (int e = 0; e < D; ++e) {
-      dv[e] = fmaf(p, gr[e], dv[e]);
-      dk[e] = fmaf(ds, qr[e], dk[e]);
-    }
-  }
-  float* dko = dK + (tok0 + j) * ld_d + head * D;
-  float* dvo = dV + (tok0 + j) * ld_d + head * D;
-  for (int e = 0; e < D; ++e) {
-    dko[e] = dk[e] * scale;
-    dvo[e] = dv[e];
-  }
-}
-
 template <int D>
 size_t fwd_lds() { return 5 * (size_t)kTL * 2 * D; }  // K: two slots, V: three
 template <int D>
@@ -1272,9 +1166,8 @@ void fwd_d(Dt dt, const AttnShape& a, const void* q, const void* k, const void* 
       attn_fwd_combine<D><<<combine_grid(a), 256, 0, s>>>(po, plse, p.fwd_chunk, (bf16*)o, ld_o,
                                                           lse, a.batch, a.seq, a.heads, a.window);
   } else {
-    dim3 g((a.seq + 63) / 64, a.heads, a.batch);
-    attn_fwd_f32<D><<<g, 64, 0, s>>>((const float*)q, (const float*)k, (const float*)v, ld,
-                                     (float*)o, ld_o, lse, a.seq, a.heads, a.window, scale);
+    launch_attn_forward_f32(a, (const float*)q, (const float*)k, (const float*)v, ld, (float*)o,
+                            ld_o, lse, s);
   }
 }
 
@@ -1313,16 +1206,9 @@ void bwd_d(Dt dt, const AttnShape& a, const void* q, const void* k, const void* 
           pdq, nullptr, p.fwd_chunk, (bf16*)dq, nullptr, ld_d, a.batch, a.seq, a.heads,
           a.window);
   } else {
-    if (!delta_ready)
-      attn_delta_kernel<float><<<(nrows + 255) / 256, 256, 0, s>>>(
-        (const float*)o, ld_o, (const float*)d_o, ld_do, delta, a.batch, a.seq, a.heads, D);
-    dim3 g((a.seq + 63) / 64, a.heads, a.batch);
-    attn_dq_f32<D><<<g, 64, 0, s>>>((const float*)q, (const float*)k, (const float*)v, ld,
-                                    (const float*)d_o, ld_do, lse, delta, (float*)dq, ld_d,
-                                    a.seq, a.heads, a.window, scale);
-    attn_dkdv_f32<D><<<g, 64, 0, s>>>((const float*)q, (const float*)k, (const float*)v, ld,
-                                      (const float*)d_o, ld_do, lse, delta, (float*)dk,
-                                      (float*)dv, ld_d, a.seq, a.heads, a.window, scale);
+    launch_attn_backward_f32(a, (const float*)q, (const float*)k, (const float*)v, ld,
+                             (const float*)o, ld_o, (const float*)d_o, ld_do, lse, delta,
+                             (float*)dq, (float*)dk, (float*)dv, ld_d, s);
   }
 }
 

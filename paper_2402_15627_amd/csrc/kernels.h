@@ -233,5 +233,13 @@ void launch_attn_backward(Dt dt, const AttnShape& a, const void* q, const void* 
                           int ld_qkv, const void* o, int ld_o, const void* d_o, int ld_do,
                           const float* lse, float* delta, bool delta_ready, void* dq, void* dk,
                           void* dv, int ld_d, void* part, size_t part_bytes, hipStream_t s);
+// The fp32 forms of the two (attn_f32.hip), never split; the backward always
+// forms delta.
+void launch_attn_forward_f32(const AttnShape& a, const float* q, const float* k, const float* v,
+                             int ld_qkv, float* o, int ld_o, float* lse, hipStream_t s);
+void launch_attn_backward_f32(const AttnShape& a, const float* q, const float* k, const float* v,
+                              int ld_qkv, const float* o, int ld_o, const float* d_o, int ld_do,
+                              const float* lse, float* delta, float* dq, float* dk, float* dv,
+                              int ld_d, hipStream_t s);
 
 }  // namespace pb
