@@ -772,26 +772,51 @@ __global__ __launch_bounds__(256) void attn_sum_combine(const float* __restrict_
 }
 
 // ===================================================== backward: delta
-template <typename T>
-__global__ __launch_bounds__(256) void attn_delta_kernel(const T* __restrict__ O, int ld_o,
-                                                         const T* __restrict__ dO, int ld_do,
-                                                         float* __restrict__ delta, int B, int S,
-                                                         int H, int D) {
-  const int idx = blockIdx.x * 256 + threadIdx.x;  // (b, t, head)
-  if (idx >= B * S * H) return;
-  const int head = idx % H, bt = idx / H;
-  const int b = bt / S, t = bt % S;
-  const T* o = O + (size_t)bt * ld_o + head * D;
-  const T* g = dO + (size_t)bt * ld_do + head * D;
-  float acc = 0.f;
-  for (int e = 0; e < D; e += 8) {
-    float a[8], c[8];
-    load8(o + e, a);
-    load8(g + e, c);
+// delta = rowsum(dO O) per head.  HBM-bound: both operands read once, D / 8
+// lanes (four for head dim 96, three chunks each) on 16-byte chunks of a row,
+// all of a thread's loads issued before the sums.  A workgroup takes
+// kDeltaRows tokens of one head, so that its stores cover whole runs of delta;
+// heads run fastest over the grid, so that neighbouring workgroups read
+// neighbouring columns of the same rows.  8192 tokens, 40 heads of 128: 152 us
+// with one thread per row, 29 us now (168 MB, 5.8 TB/s).
+constexpr int kDeltaRows = 64;
+template <int D>
+__global__ __launch_bounds__(256) void attn_delta_kernel(const bf16* __restrict__ O, int ld_o,
+                                                         const bf16* __restrict__ dO, int ld_do,
+                                                         float* __restrict__ delta, int S, int H) {
+  constexpr int kLanes = D == 96 ? 4 : D / 8;   // per row
+  constexpr int kChunks = D / 8 / kLanes;       // per lane
+  constexpr int kPass = 256 / kLanes;           // rows at a time
+  constexpr int kN = kDeltaRows / kPass;
+  static_assert(kPass <= kDeltaRows && kDeltaRows % kPass == 0, "whole passes");
+  const int head = blockIdx.x % H, b = blockIdx.z, l = threadIdx.x % kLanes;
+  const int t0 = blockIdx.x / H * kDeltaRows + threadIdx.x / kLanes;
+  u32x4 o[kN][kChunks], g[kN][kChunks];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc += a[i] * c[i];
+  for (int n = 0; n < kN; ++n) {
+    const size_t row = (size_t)b * S + min(t0 + n * kPass, S - 1);
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      const int e = head * D + 8 * (l + c * kLanes);
+      o[n][c] = *reinterpret_cast<const u32x4*>(O + row * ld_o + e);
+      g[n][c] = *reinterpret_cast<const u32x4*>(dO + row * ld_do + e);
+    }
   }
-  delta[((size_t)b * H + head) * S + t] = acc;
+#pragma unroll
+  for (int n = 0; n < kN; ++n) {
+    float acc = 0.f;
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        acc = fmaf(lo_bf(o[n][c][i]), lo_bf(g[n][c][i]), acc);
+        acc = fmaf(hi_bf(o[n][c][i]), hi_bf(g[n][c][i]), acc);
+      }
+#pragma unroll
+    for (int off = 1; off < kLanes; off <<= 1) acc += __shfl_xor(acc, off, 64);
+    const int t = t0 + n * kPass;
+    if (l == 0 && t < S) delta[((size_t)b * H + head) * S + t] = acc;
+  }
 }
 
 // ====================================================== backward: dK, dV
@@ -1177,11 +1202,11 @@ void bwd_d(Dt dt, const AttnShape& a, const void* q, const void* k, const void* 
            bool delta_ready, void* dq, void* dk, void* dv, int ld_d, void* part,
            size_t part_bytes, hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)D);
-  const int nrows = a.batch * a.seq * a.heads;
   if (dt == Dt::BF16) {
     if (!delta_ready)
-      attn_delta_kernel<bf16><<<(nrows + 255) / 256, 256, 0, s>>>(
-          (const bf16*)o, ld_o, (const bf16*)d_o, ld_do, delta, a.batch, a.seq, a.heads, D);
+      attn_delta_kernel<D><<<dim3((unsigned)a.heads * ((a.seq + kDeltaRows - 1) / kDeltaRows), 1, a.batch),
+                             256, 0, s>>>((const bf16*)o, ld_o, (const bf16*)d_o, ld_do, delta, a.seq,
+                                  a.heads);
     AttnSplit p = attn_bwd_split_plan(dt, a);
     if (!part || part_bytes < attn_bwd_partial_bytes(a, p)) {
       p.fwd_chunk = p.kv_chunk = kUnsplit;
