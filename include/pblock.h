@@ -364,7 +364,7 @@ pb_status pblock_swattn_backward(const pb_config* cfg, const void* q,
 
 /* ------------------------------------------------ tensor-parallel context
  * The HIP events with which pblock_ag_in_proj and pblock_rs_out_proj order
- * their copy streams against the GEMM stream: 3 tp + 1 events, created by
+ * their copy streams against the GEMM stream, created by
  * pblock_tp_context_create on the device current at that call, with timing
  * disabled.  A context serves calls with the same tp on that device, one
  * after another (re-recording an event between calls is safe: a stream

@@ -84,6 +84,16 @@ struct RsParts {
 void launch_rs_reduce(Dt dt, const RsParts& parts, const void* x, const void* bias, void* y,
                       int rows, int H, hipStream_t s);
 
+// ------------------------------------------------------------ shard copies
+// dst[i][0 .. bytes) = src[i][0 .. bytes) for i < n, buffers of this GPU,
+// 16-byte aligned, bytes a multiple of 16, no overlap.
+struct CopyList {
+  const void* src[kRsMaxParts];
+  void* dst[kRsMaxParts];
+  int n;
+};
+void launch_copies(const CopyList& list, size_t bytes, hipStream_t s);
+
 // ------------------------------------------------------------------ GEMMs
 // C[m, n] = sum_k A(m, k) B(k, n), fp32 accumulation.
 // A(m, k) is A[m * lda + k] when a_kcontig, else A[k * lda + m]; B(k, n) is

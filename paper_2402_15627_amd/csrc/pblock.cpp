@@ -1199,15 +1199,14 @@ constexpr int kAgMaxComm = 8;
 constexpr int kAgMaxTp = 64;
 }  // namespace
 
-// Events of the pipelined all-gather and reduce-scatter calls, tp of each
-// kind plus one, on one device.
+// Events of the pipelined all-gather and reduce-scatter calls, on one device.
 struct pb_tp_context {
   int device;
   int tp;
   hipEvent_t start;             // AG: the work on `stream` before the copies
-  hipEvent_t landed[kAgMaxTp];  // AG: per position in the ring order
+  hipEvent_t landed[kAgMaxTp];  // AG: per position in the ring order (the last of a copy launch)
   hipEvent_t computed[kAgMaxTp];// RS: per launch group, on `stream`
-  hipEvent_t sent[kAgMaxTp];    // RS: per chunk, on its comm stream
+  hipEvent_t sent[kAgMaxComm];  // RS: per comm stream, after its last chunk
 };
 
 pb_status pblock_tp_context_create(int tp, pb_tp_context** ctx) {
@@ -1225,8 +1224,8 @@ pb_status pblock_tp_context_create(int tp, pb_tp_context** ctx) {
   for (int i = 0; i < tp; ++i) {
     make(&c->landed[i]);
     make(&c->computed[i]);
-    make(&c->sent[i]);
   }
+  for (hipEvent_t& e : c->sent) make(&e);
   if (!ok) {
     pblock_tp_context_destroy(c);
     return fail(PB_ERR_HIP, "hipEventCreateWithFlags failed");
@@ -1244,8 +1243,8 @@ void pblock_tp_context_destroy(pb_tp_context* ctx) {
   for (int i = 0; i < ctx->tp; ++i) {
     drop(ctx->landed[i]);
     drop(ctx->computed[i]);
-    drop(ctx->sent[i]);
   }
+  for (hipEvent_t e : ctx->sent) drop(e);
   delete ctx;
 }
 
@@ -1301,6 +1300,35 @@ bool tp_args_ok(const pb_config* cfg, int tp, int per_launch) {
          per_launch <= tp && dims_of(cfg).T % tp == 0;
 }
 
+// The copies of one launch group on one comm stream.  Between buffers of this
+// GPU a kernel copies them all (memory-bound, ~4 TB/s; the DMA engines move
+// ~150 GB/s between local buffers, which then set the pace of the whole
+// pipeline: 2048 x 12288 bf16 rows over 8 ranks 707 -> 576 us for the
+// all-gather into the in-projection, 599 -> 508 us for the out-projection
+// into the reduce-scatter).  A list with a buffer of another GPU goes to the
+// DMA engines, which need no mapping of it here and leave the CUs to the GEMM.
+pb_status copy_on(const pb::CopyList& list, size_t bytes, int device, hipStream_t s) {
+  auto local = [&](const void* p) {
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+      (void)hipGetLastError();  // not an error of this call: the copy reports its own
+      return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == device;
+  };
+  bool all = true;
+  for (int i = 0; i < list.n; ++i) all = all && local(list.src[i]) && local(list.dst[i]);
+  if (all) {
+    pb::launch_copies(list, bytes, s);
+    return PB_OK;
+  }
+  for (int i = 0; i < list.n; ++i)
+    if (hipMemcpyAsync(list.dst[i], list.src[i], bytes, hipMemcpyDeviceToDeviceNoCU, s) !=
+        hipSuccess)
+      return fail(PB_ERR_HIP, "hipMemcpyAsync of a shard failed");
+  return PB_OK;
+}
+
 // All-gather pipelined into a row-parallel GEMM: the shards are copied into
 // `gathered` on the comm streams in ring order from `rank` (the k-th on
 // comm_streams[k % n_comm]); gemm_rows(j0, n) computes the GEMM over the
@@ -1329,39 +1357,49 @@ pb_status ag_pipeline(int tp, int rank, const void* const* shards, void* gathere
       if (!ok(hipStreamWaitEvent(comm_streams[i], ev.start, 0)))
         return fail(PB_ERR_HIP, "hipStreamWaitEvent failed");
   }
-  for (int k = 0; k < tp; ++k) {
-    const int j = (rank + k) % tp;
-    if (in_place(j)) continue;
-    hipStream_t cs = comm_streams[k % n_comm];
-    char* dst = (char*)gathered + (size_t)j * shard_bytes;
-    if (!ok(hipMemcpyAsync(dst, shards[j], shard_bytes, hipMemcpyDeviceToDeviceNoCU, cs)))
-      return fail(PB_ERR_HIP, "hipMemcpyAsync of shard %d failed", j);
-    if (!ok(hipEventRecord(ev.landed[k], cs))) return fail(PB_ERR_HIP, "hipEventRecord failed");
-  }
+  // launch groups: positions [first[n], first[n + 1])
   int ready = 0;
   while (ready < tp && in_place((rank + ready) % tp)) ++ready;
-  auto launch_group = [&](int k0, int k1, bool wait) -> bool {
-    if (wait)
-      for (int k = k0; k < k1; ++k)
-        if (!in_place((rank + k) % tp) && !ok(hipStreamWaitEvent(stream, ev.landed[k], 0)))
-          return false;
-    const int j0 = (rank + k0) % tp, n = k1 - k0;
-    if (j0 + n <= tp) {
-      gemm_rows(j0, n);
-    } else {
-      gemm_rows(j0, tp - j0);
-      gemm_rows(0, j0 + n - tp);
-    }
-    return true;
-  };
+  int first[kAgMaxTp + 2], groups = 0;
   int k0 = 0;
   if (ready > 0 && ready < tp && per_launch < tp) {
-    if (!launch_group(0, ready, false)) return fail(PB_ERR_HIP, "hipStreamWaitEvent failed");
+    first[groups++] = 0;
     k0 = ready;
   }
-  for (; k0 < tp; k0 += per_launch)
-    if (!launch_group(k0, std::min(tp, k0 + per_launch), true))
-      return fail(PB_ERR_HIP, "hipStreamWaitEvent failed");
+  for (; k0 < tp; k0 += per_launch) first[groups++] = k0;
+  first[groups] = tp;
+  // one copy launch per group and comm stream, and the event the group's GEMM
+  // waits for
+  hipEvent_t landed[kAgMaxTp][kAgMaxComm] = {};
+  for (int n = 0; n < groups; ++n)
+    for (int i = 0; i < n_comm; ++i) {
+      pb::CopyList list{};
+      int last = -1;
+      for (int k = first[n]; k < first[n + 1]; ++k) {
+        const int j = (rank + k) % tp;
+        if (k % n_comm != i || in_place(j)) continue;
+        list.src[list.n] = shards[j];
+        list.dst[list.n++] = (char*)gathered + (size_t)j * shard_bytes;
+        last = k;
+      }
+      if (!list.n) continue;
+      PB_CHECK(copy_on(list, shard_bytes, ev.device, comm_streams[i]));
+      landed[n][i] = ev.landed[last];
+      if (!ok(hipEventRecord(landed[n][i], comm_streams[i])))
+        return fail(PB_ERR_HIP, "hipEventRecord failed");
+    }
+  for (int n = 0; n < groups; ++n) {
+    for (int i = 0; i < n_comm; ++i)
+      if (landed[n][i] && !ok(hipStreamWaitEvent(stream, landed[n][i], 0)))
+        return fail(PB_ERR_HIP, "hipStreamWaitEvent failed");
+    const int j0 = (rank + first[n]) % tp, count = first[n + 1] - first[n];
+    if (j0 + count <= tp) {
+      gemm_rows(j0, count);
+    } else {
+      gemm_rows(j0, tp - j0);
+      gemm_rows(0, j0 + count - tp);
+    }
+  }
   return PB_OK;
 }
 
@@ -1377,6 +1415,7 @@ pb_status rs_pipeline(int tp, int rank, const void* partial, void* const* dst, s
                       const hipStream_t* comm_streams, pb_tp_context& ev, F gemm_rows) {
   auto ok = [](hipError_t e) { return e == hipSuccess; };
   int group = 0;
+  bool used[kAgMaxComm] = {};
   for (int k0 = 0; k0 < tp; k0 += per_launch, ++group) {
     const int k1 = std::min(tp, k0 + per_launch);
     const int j0 = (rank + 1 + k0) % tp, n = k1 - k0;
@@ -1386,28 +1425,34 @@ pb_status rs_pipeline(int tp, int rank, const void* partial, void* const* dst, s
       gemm_rows(j0, tp - j0);
       gemm_rows(0, j0 + n - tp);
     }
+    // the group's chunks, one copy launch per comm stream
     bool recorded = false;
-    for (int k = k0; k < k1; ++k) {
-      const int j = (rank + 1 + k) % tp;
-      const char* src = (const char*)partial + (size_t)j * chunk_bytes;
-      if (dst[j] == src) continue;  // in place: nothing to send or wait for
-      if (!recorded) {
-        if (!ok(hipEventRecord(ev.computed[group], stream)))
-          return fail(PB_ERR_HIP, "hipEventRecord failed");
-        recorded = true;
+    for (int i = 0; i < n_comm; ++i) {
+      pb::CopyList list{};
+      for (int k = k0; k < k1; ++k) {
+        const int j = (rank + 1 + k) % tp;
+        const char* src = (const char*)partial + (size_t)j * chunk_bytes;
+        // a chunk in place has nothing to send or wait for
+        if (k % n_comm != i || dst[j] == src) continue;
+        list.src[list.n] = src;
+        list.dst[list.n++] = dst[j];
       }
-      hipStream_t cs = comm_streams[k % n_comm];
+      if (!list.n) continue;
+      if (!recorded && !ok(hipEventRecord(ev.computed[group], stream)))
+        return fail(PB_ERR_HIP, "hipEventRecord failed");
+      recorded = true;
+      hipStream_t cs = comm_streams[i];
       if (!ok(hipStreamWaitEvent(cs, ev.computed[group], 0)))
         return fail(PB_ERR_HIP, "hipStreamWaitEvent failed");
-      if (!ok(hipMemcpyAsync(dst[j], src, chunk_bytes, hipMemcpyDeviceToDeviceNoCU, cs)))
-        return fail(PB_ERR_HIP, "hipMemcpyAsync of chunk %d failed", j);
-      if (!ok(hipEventRecord(ev.sent[k], cs))) return fail(PB_ERR_HIP, "hipEventRecord failed");
+      PB_CHECK(copy_on(list, chunk_bytes, ev.device, cs));
+      used[i] = true;
     }
   }
-  for (int k = 0; k < tp; ++k) {
-    const int j = (rank + 1 + k) % tp;
-    if (dst[j] == (const char*)partial + (size_t)j * chunk_bytes) continue;
-    if (!ok(hipStreamWaitEvent(stream, ev.sent[k], 0)))
+  for (int i = 0; i < n_comm; ++i) {
+    if (!used[i]) continue;
+    if (!ok(hipEventRecord(ev.sent[i], comm_streams[i])))
+      return fail(PB_ERR_HIP, "hipEventRecord failed");
+    if (!ok(hipStreamWaitEvent(stream, ev.sent[i], 0)))
       return fail(PB_ERR_HIP, "hipStreamWaitEvent failed");
   }
   return PB_OK;

@@ -44,7 +44,31 @@ __global__ __launch_bounds__(kRsThreads) void rs_reduce_kernel(RsParts parts, co
   store8<T>(y + off, acc);
 }
 
+// Copies of whole shards between buffers of this GPU, the list's entries side
+// by side in one launch.  HBM-bound: each thread has kCopyVec 16-byte loads in
+// flight before its first store; small workgroups of few registers, so that
+// they fit next to a GEMM's and drain quickly.
+constexpr int kCopyThreads = 256, kCopyVec = 4;
+__global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyList list, size_t vecs) {
+  const u32x4* __restrict__ src = (const u32x4*)list.src[blockIdx.y];
+  u32x4* __restrict__ dst = (u32x4*)list.dst[blockIdx.y];
+  const size_t i0 = (size_t)blockIdx.x * (kCopyThreads * kCopyVec) + threadIdx.x;
+  u32x4 v[kCopyVec];
+#pragma unroll
+  for (int n = 0; n < kCopyVec; ++n)
+    if (i0 + n * kCopyThreads < vecs) v[n] = src[i0 + n * kCopyThreads];
+#pragma unroll
+  for (int n = 0; n < kCopyVec; ++n)
+    if (i0 + n * kCopyThreads < vecs) dst[i0 + n * kCopyThreads] = v[n];
+}
+
 }  // namespace
+
+void launch_copies(const CopyList& list, size_t bytes, hipStream_t s) {
+  const size_t vecs = bytes / 16, per = kCopyThreads * kCopyVec;
+  if (!list.n || !vecs) return;
+  copy_kernel<<<dim3((unsigned)((vecs + per - 1) / per), list.n), kCopyThreads, 0, s>>>(list, vecs);
+}
 
 void launch_rs_reduce(Dt dt, const RsParts& parts, const void* x, const void* bias, void* y,
                       int rows, int H, hipStream_t s) {
