@@ -240,11 +240,10 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x,
  * into `splits` K-slices whose fp32 partial tiles a second kernel sums.
  * Fills tiles, n_full (tiles computed whole), tail, splits (1: no split),
  * workgroups (of the GEMM kernel: n_full + tail * splits) and threads (per
- * workgroup).  bf16 with K % 64 == 0 takes the matrix-core path that splits;
- * other bf16 GEMMs launch unsplit.  fp32 GEMMs have tiles of 64 x 64, all of
- * them split along K where that is estimated to be faster (n_full is 0 then,
- * and tail counts the 256 x 256 blocks of the output that the workspace holds
- * `splits` times), or, in small grids, whole tiles of 16 x 64.
+ * workgroup).  fp32 GEMMs have tiles of 64 x 64, all of them split along K
+ * where that is estimated to be faster (n_full is 0 then, and tail counts the
+ * 256 x 256 blocks of the output that the workspace holds `splits` times), or,
+ * in small grids, whole tiles of 16 x 64.
  *
  * pblock_backward_pairs: which backward GEMMs share one launch with the
  * weight-gradient GEMM after them (1) or launch alone (0).  block 0, the

@@ -2,12 +2,12 @@
 //
 // bf16 path: 256x256 output tile per workgroup of eight waves (each wave
 // 64x128).  Two kernels share the tile, the wave layout and the epilogues:
-//   - K a multiple of 64 (every GEMM of the block at the benchmarked sizes):
-//     MFMA v_mfma_f32_16x16x32_bf16, operands reach LDS by LDS-DMA, K-tiles
-//     of 64 through two stages, fragments read two phases ahead and the
-//     barrier placed before the K-tile's last two phases (see the DMA kernel
-//     below);
-//   - otherwise (ragged token counts in the weight-gradient GEMMs): MFMA
+//   - the LDS-DMA kernel: MFMA v_mfma_f32_16x16x32_bf16, operands reach LDS
+//     by LDS-DMA, K-tiles of 64 through two stages, fragments read two phases
+//     ahead and the barrier placed before the K-tile's last two phases (see
+//     the DMA kernel below); a build of its own (RK) for K that is no
+//     multiple of 64;
+//   - for operands whose tile offsets exceed 32 bits: MFMA
 //     v_mfma_f32_32x32x16_bf16, K-tile 64, double-buffered LDS, loads staged
 //     through registers with zero fill; an M- or N-contiguous operand is
 //     loaded as 8x8 blocks and transposed in registers on its way into LDS.
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_kernel(const bf16* __re
 }
 
 // ------------------------------------------- bf16 MFMA GEMM, LDS-DMA path
-// Used when K is a multiple of 64.  The operand tiles go from global memory
+// The operand tiles go from global memory
 // straight into LDS (global_load_lds_dwordx4: each lane's 16 bytes land at
 // LDS base + 16 * lane), so there is no register staging and no LDS write
 // instruction.  K-tiles of 64 (a K-contiguous row then spans whole 128-byte
@@ -314,18 +314,27 @@ PB_DEV void block_barrier() {
 // KC: row r of the tile at X[(R0 + r) * ld + k]; rows past Rmax are clamped
 // (their results are never stored).  Else X[k * ld + R0 + c], columns past
 // Rmax clamped the same way.
+// k past `left` (a K-tile that the operand ends in) is clamped too, to k the
+// operand holds: the caller overwrites those 16 bytes with zeros.
 template <bool KC>
-PB_DEV uint32_t dma_lane_off(int ld, int R0, int Rmax, int wave, int lane, int i) {
+PB_DEV uint32_t dma_lane_off(int ld, int R0, int Rmax, int wave, int lane, int i,
+                             int left = kDK) {
   const int p = wave * (kPieces * 1024) + i * 1024 + 16 * lane;
   if constexpr (KC) {
     const int row = p >> 7, c = swz(row, (p >> 4) & 7);
     const int r = min(R0 + row, Rmax - 1) - R0;
-    return (uint32_t)(r * ld + 8 * c) * 2u;
+    return (uint32_t)(r * ld + (8 * c < left ? 8 * c : 0)) * 2u;
   } else {
     const int krow = p >> 9, c = swz_mn(krow, (p >> 4) & 31);
     const int col = min(R0 + 8 * c, Rmax - 8) - R0;
-    return (uint32_t)(krow * ld + col) * 2u;
+    return (uint32_t)(min(krow, left - 1) * ld + col) * 2u;
   }
+}
+// Whether this lane's 16 bytes of the piece lie past `left` k of the K-tile.
+template <bool KC>
+PB_DEV bool dma_lane_past(int wave, int lane, int i, int left) {
+  const int p = wave * (kPieces * 1024) + i * 1024 + 16 * lane;
+  return KC ? 8 * swz(p >> 7, (p >> 4) & 7) >= left : (p >> 9) >= left;
 }
 
 // MFMA fragment (8 bf16 along k) of tile row `row`, k-step ks, lane half h.
@@ -566,12 +575,22 @@ PB_DEV float sum_bf16x8(const bf16x8& p, float acc) {
 // queue (*qticket) right after the main loop, so the atomic's latency is
 // spent under the epilogue; and tid_in, the thread index the caller keeps
 // out of the compiler's sight (see gemm_bf16_dma_pair_persistent).
-template <bool AK, bool BK, Epi EPI, bool GT, bool RS = false>
+// RK: K is not a multiple of the K-tile, and this item's last K-tile holds
+// left_k k (64 for an item that ends before K does).  That tile is taken
+// first, so that the main loop stays as it is: its loads are clamped to k the
+// operands hold, and the wave that moved a part of it zeroes that part's k
+// past the end in LDS, between its arrival and the barrier that shows it to
+// the other waves: in both operands, so that whatever the clamped loads
+// brought in (an infinity, say) meets no product.  (A K-contiguous operand's
+// K is a multiple of 8, so its 16-byte chunks lie inside or past the end
+// whole.)  The weight gradients of a block of 2025 tokens, hidden 2048 and
+// 14336 in-projection columns: 333 us by the register-staged kernel, 205 us.
+template <bool AK, bool BK, Epi EPI, bool GT, bool RS = false, bool RK = false>
 PB_DEV void dma_gemm_item(const bf16* __restrict__ A, int lda, const bf16* __restrict__ B, int ldb,
                           int M, int N, const EpiArgs& ep, int lid, int slice, int kt0, int kt1,
                           int n_full, int splits, float* __restrict__ part,
                           int* __restrict__ qctr = nullptr, int* qticket = nullptr,
-                          int tid_in = -1) {
+                          int tid_in = -1, int left_k = kDK) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(PB_LDS unsigned char*)smem;
   auto a_off = [&](int s) { return (2 * s) * kDTile; };
@@ -622,7 +641,9 @@ PB_DEV void dma_gemm_item(const bf16* __restrict__ A, int lda, const bf16* __res
   auto issue_half = [&](int t, int half) {
     if (!dma_wave) return;
     const int s = t % kStages;
-    const bf16* src = half == 0 ? abase + (size_t)t * astep : bbase + (size_t)t * bstep;
+    // RK: tile 0 is the last K-tile, tile t K-tile t - 1
+    const size_t kt = RK ? (size_t)(t - 1) : (size_t)t;
+    const bf16* src = half == 0 ? abase + kt * astep : bbase + kt * bstep;
     const uint32_t dst0 = lds0 + (half == 0 ? a_off(s) : b_off(s));
 #pragma unroll
     for (int r = 0; r < kReg; ++r)
@@ -634,6 +655,36 @@ PB_DEV void dma_gemm_item(const bf16* __restrict__ A, int lda, const bf16* __res
   auto issue = [&](int t) {
     issue_half(t, 0);
     issue_half(t, 1);
+  };
+
+  // RK: the last K-tile, as tile 0; and zeros over its k past the end
+  auto issue_last = [&]() {
+    if (!dma_wave) return;
+    const bf16* sa = abase + (size_t)(nt - 1) * astep;
+    const bf16* sb = bbase + (size_t)(nt - 1) * bstep;
+#pragma unroll
+    for (int r = 0; r < kReg; ++r)
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i) {
+        const uint32_t at = region(r) * (kPieces * 1024) + i * 1024;
+        dma16s(sa, dma_lane_off<AK>(lda, m0, M, region(r), lane, i, left_k),
+               __builtin_amdgcn_readfirstlane(lds0 + a_off(0) + at));
+        dma16s(sb, dma_lane_off<BK>(ldb, n0, N, region(r), lane, i, left_k),
+               __builtin_amdgcn_readfirstlane(lds0 + b_off(0) + at));
+      }
+  };
+  auto zero_last = [&]() {
+    if (left_k == kDK || !dma_wave) return;
+#pragma unroll
+    for (int r = 0; r < kReg; ++r)
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i) {
+        const int at = region(r) * (kPieces * 1024) + i * 1024 + 16 * lane;
+        if (dma_lane_past<AK>(region(r), lane, i, left_k))
+          *reinterpret_cast<u32x4*>(smem + a_off(0) + at) = u32x4{0, 0, 0, 0};
+        if (dma_lane_past<BK>(region(r), lane, i, left_k))
+          *reinterpret_cast<u32x4*>(smem + b_off(0) + at) = u32x4{0, 0, 0, 0};
+      }
   };
 
   f32x4 acc[kTM16][kTN16];
@@ -728,10 +779,15 @@ PB_DEV void dma_gemm_item(const bf16* __restrict__ A, int lda, const bf16* __res
   pin_sgpr(ep.col2), pin_sgpr(ep.mean), pin_sgpr(ep.rstd), pin_sgpr(ep.rowpart);
   pin_sgpr(ep.rowpart_ld), pin_sgpr(part), pin_sgpr(ep.o_rows), pin_sgpr(ep.ld_o_rows);
   pin_sgpr(ep.delta), pin_sgpr(ep.delta_seq), pin_sgpr(ep.delta_heads), pin_sgpr(ep.delta_hd);
-  if (nt > 0) issue(0);
+  if (nt > 0) {
+    if constexpr (RK) issue_last();
+    else issue(0);
+  }
   if (nt > 1) issue(1);
   if (nt > 1) wait_dma<kDmaPerTile>();  // tile 0 landed; tile 1 may be in flight
   else wait_dma<0>();
+  if constexpr (RK)
+    if (nt > 0) zero_last();
   block_barrier();
   // batch by batch, as in the loop, so the wait at the loop's head (merged
   // over both ways in) can leave the later batches in flight
@@ -775,7 +831,7 @@ PB_DEV void dma_gemm_item(const bf16* __restrict__ A, int lda, const bf16* __res
   }
 }
 
-template <bool AK, bool BK, Epi EPI, bool GT>
+template <bool AK, bool BK, Epi EPI, bool GT, bool RK = false>
 __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_dma_kernel(const bf16* __restrict__ A,
                                                                     int lda,
                                                                     const bf16* __restrict__ B,
@@ -784,7 +840,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_dma_kernel(const bf16* 
                                                                     int splits,
                                                                     float* __restrict__ part) {
   const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
-  const int nk_all = K / kBK;  // slices are planned in units of 64
+  const int nk_all = RK ? (K + kBK - 1) / kBK : K / kBK;  // slices are planned in units of 64
   int lid, slice = -1, kt0 = 0, kt1 = nk_all;
   if ((int)blockIdx.x < n_full) {
     lid = xcd_remap(blockIdx.x, n_full);
@@ -797,8 +853,9 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_dma_kernel(const bf16* 
     kt0 = min(nk_all, slice * chunk);
     kt1 = min(nk_all, kt0 + chunk);
   }
-  dma_gemm_item<AK, BK, EPI, GT>(A, lda, B, ldb, M, N, ep, lid, slice, kt0, kt1, n_full, splits,
-                                 part);
+  const int left = RK && kt1 == nk_all ? K - (nk_all - 1) * kBK : kDK;
+  dma_gemm_item<AK, BK, EPI, GT, false, RK>(A, lda, B, ldb, M, N, ep, lid, slice, kt0, kt1, n_full,
+                                            splits, part, nullptr, nullptr, -1, left);
 }
 
 // Two independent GEMMs in one launch, neither split: workgroups 0 ..
@@ -999,37 +1056,27 @@ bool dma_offsets_fit(bool ak, int lda, bool bk, int ldb) {
 }
 
 template <bool AK, bool BK, Epi EPI, bool GT>
-void gemm_dispatch_layout(Dt dt, const void* A, int lda, const void* B, int ldb, int M, int N,
-                          int K, const EpiArgs& ep, float* split_ws, size_t split_ws_floats,
-                          hipStream_t s) {
-  if (dt == Dt::BF16) {
-    const int tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
-    const size_t lds = 4 * (size_t)kTileBytes;  // both kernels: 128 KB
-    static_assert(kStages * 2 * kDTile == 4 * kTileBytes, "DMA path LDS");
-    if (K % kBK == 0 && dma_offsets_fit(AK, lda, BK, ldb)) {
-      SplitPlan sp = gemm_split_plan(dt, M, N, K);
-      if (sp.tail > 0 && (!split_ws || split_ws_floats < gemm_split_floats(dt, M, N, K)))
-        sp = SplitPlan{tiles, 0, 1};
-      gemm_bf16_dma_kernel<AK, BK, EPI, GT><<<sp.n_full + sp.tail * sp.splits, kThreads, lds, s>>>(
-          (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, ep, sp.n_full, sp.splits, split_ws);
-      if (sp.tail > 0)
-        splitk_reduce<EPI, GT><<<sp.tail * 64, 256, 0, s>>>(split_ws, M, N, sp.n_full, sp.splits, ep);
-    } else
-      gemm_bf16_kernel<AK, BK, EPI, GT><<<tiles, kThreads, lds, s>>>(
-          (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, ep);
-  } else {
-    launch_gemm_f32(EPI, AK, BK, (const float*)A, lda, (const float*)B, ldb, M, N, K, ep,
-                    split_ws, split_ws_floats, s);
+void gemm_dispatch(Dt dt, const void* A, int lda, const void* B, int ldb, int M, int N, int K,
+                   const EpiArgs& ep, float* split_ws, size_t split_ws_floats, hipStream_t s) {
+  const int tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
+  const size_t lds = 4 * (size_t)kTileBytes;  // both kernels: 128 KB
+  static_assert(kStages * 2 * kDTile == 4 * kTileBytes, "DMA path LDS");
+  if (!dma_offsets_fit(AK, lda, BK, ldb)) {
+    gemm_bf16_kernel<AK, BK, EPI, GT><<<tiles, kThreads, lds, s>>>(
+        (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, ep);
+    return;
   }
-}
-
-template <Epi EPI, bool GT>
-void gemm_dispatch(Dt dt, bool ak, bool bk, const void* A, int lda, const void* B, int ldb,
-                   int M, int N, int K, const EpiArgs& ep, float* ws, size_t wsf, hipStream_t s) {
-  if (ak && bk) gemm_dispatch_layout<true, true, EPI, GT>(dt, A, lda, B, ldb, M, N, K, ep, ws, wsf, s);
-  else if (ak) gemm_dispatch_layout<true, false, EPI, GT>(dt, A, lda, B, ldb, M, N, K, ep, ws, wsf, s);
-  else if (bk) gemm_dispatch_layout<false, true, EPI, GT>(dt, A, lda, B, ldb, M, N, K, ep, ws, wsf, s);
-  else gemm_dispatch_layout<false, false, EPI, GT>(dt, A, lda, B, ldb, M, N, K, ep, ws, wsf, s);
+  SplitPlan sp = gemm_split_plan(dt, M, N, K);
+  if (sp.tail > 0 && (!split_ws || split_ws_floats < gemm_split_floats(dt, M, N, K)))
+    sp = SplitPlan{tiles, 0, 1};
+  auto run = [&](auto kernel) {
+    kernel<<<sp.n_full + sp.tail * sp.splits, kThreads, lds, s>>>(
+        (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, ep, sp.n_full, sp.splits, split_ws);
+  };
+  if (K % kBK == 0) run(gemm_bf16_dma_kernel<AK, BK, EPI, GT>);
+  else run(gemm_bf16_dma_kernel<AK, BK, EPI, GT, true>);
+  if (sp.tail > 0)
+    splitk_reduce<EPI, GT><<<sp.tail * 64, 256, 0, s>>>(split_ws, M, N, sp.n_full, sp.splits, ep);
 }
 
 }  // namespace
@@ -1037,8 +1084,8 @@ void gemm_dispatch(Dt dt, bool ak, bool bk, const void* A, int lda, const void* 
 SplitPlan gemm_split_plan(Dt dt, int M, int N, int K) {
   const int tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
   SplitPlan none{tiles, 0, 1};
-  if (dt != Dt::BF16 || K % kBK != 0) return none;
-  const int nk = K / kBK;
+  if (dt != Dt::BF16) return none;
+  const int nk = (K + kBK - 1) / kBK;
   const int n_full = tiles / kCUs * kCUs;
   const int tail = tiles - n_full;
   if (tail == 0) return none;
@@ -1134,30 +1181,33 @@ bool launch_gemm_pair(Dt dt, const GemmSpec& g1, const GemmSpec& g2, int* queue,
   return true;
 }
 
+// The layouts below are the ones the block and the pipelined calls use; the
+// callers pass no others.
 void launch_gemm(Dt dt, Epi epi, bool a_kcontig, bool b_kcontig, const void* A, int lda,
                  const void* B, int ldb, int M, int N, int K, const EpiArgs& ep, float* split_ws,
                  size_t split_ws_floats, hipStream_t s) {
+  if (dt == Dt::F32) {
+    launch_gemm_f32(epi, a_kcontig, b_kcontig, (const float*)A, lda, (const float*)B, ldb, M, N, K,
+                    ep, split_ws, split_ws_floats, s);
+    return;
+  }
   const bool gt = ep.gelu_tanh != 0;
-  float* w = split_ws;
-  const size_t wf = split_ws_floats;
+  auto run = [&](auto dispatch) {
+    dispatch(dt, A, lda, B, ldb, M, N, K, ep, split_ws, split_ws_floats, s);
+  };
   switch (epi) {
-    case Epi::StoreF32:
-      gemm_dispatch<Epi::StoreF32, true>(dt, a_kcontig, b_kcontig, A, lda, B, ldb, M, N, K, ep, w, wf, s);
-      break;
+    case Epi::StoreF32: run(gemm_dispatch<false, false, Epi::StoreF32, true>); break;
     case Epi::BiasGelu:
-      if (gt) gemm_dispatch<Epi::BiasGelu, true>(dt, a_kcontig, b_kcontig, A, lda, B, ldb, M, N, K, ep, w, wf, s);
-      else gemm_dispatch<Epi::BiasGelu, false>(dt, a_kcontig, b_kcontig, A, lda, B, ldb, M, N, K, ep, w, wf, s);
+      if (gt) run(gemm_dispatch<true, true, Epi::BiasGelu, true>);
+      else run(gemm_dispatch<true, true, Epi::BiasGelu, false>);
       break;
-    case Epi::BiasResid:
-      gemm_dispatch<Epi::BiasResid, true>(dt, a_kcontig, b_kcontig, A, lda, B, ldb, M, N, K, ep, w, wf, s);
-      break;
+    case Epi::BiasResid: run(gemm_dispatch<true, true, Epi::BiasResid, true>); break;
     case Epi::DgeluSplit:
-      if (gt) gemm_dispatch<Epi::DgeluSplit, true>(dt, a_kcontig, b_kcontig, A, lda, B, ldb, M, N, K, ep, w, wf, s);
-      else gemm_dispatch<Epi::DgeluSplit, false>(dt, a_kcontig, b_kcontig, A, lda, B, ldb, M, N, K, ep, w, wf, s);
+      if (b_kcontig) run(gemm_dispatch<true, true, Epi::DgeluSplit, true>);  // plain stores
+      else if (gt) run(gemm_dispatch<true, false, Epi::DgeluSplit, true>);
+      else run(gemm_dispatch<true, false, Epi::DgeluSplit, false>);
       break;
-    case Epi::LnGrad:
-      gemm_dispatch<Epi::LnGrad, true>(dt, a_kcontig, b_kcontig, A, lda, B, ldb, M, N, K, ep, w, wf, s);
-      break;
+    case Epi::LnGrad: run(gemm_dispatch<true, false, Epi::LnGrad, true>); break;
   }
 }
 

@@ -458,15 +458,6 @@ void launch_layout(const float* A, int lda, const float* B, int ldb, int M, int 
   }
 }
 
-template <Epi EPI, bool GT>
-void launch_epi(bool ak, bool bk, const float* A, int lda, const float* B, int ldb, int M, int N,
-                int K, const EpiArgs& ep, float* ws, size_t wsf, hipStream_t s) {
-  if (ak && bk) launch_layout<true, true, EPI, GT>(A, lda, B, ldb, M, N, K, ep, ws, wsf, s);
-  else if (ak) launch_layout<true, false, EPI, GT>(A, lda, B, ldb, M, N, K, ep, ws, wsf, s);
-  else if (bk) launch_layout<false, true, EPI, GT>(A, lda, B, ldb, M, N, K, ep, ws, wsf, s);
-  else launch_layout<false, false, EPI, GT>(A, lda, B, ldb, M, N, K, ep, ws, wsf, s);
-}
-
 }  // namespace
 
 GemmLaunch gemm_f32_launch_of(int M, int N, int K) {
@@ -476,22 +467,21 @@ GemmLaunch gemm_f32_launch_of(int M, int N, int K) {
 void launch_gemm_f32(Epi epi, bool a_kcontig, bool b_kcontig, const float* A, int lda,
                      const float* B, int ldb, int M, int N, int K, const EpiArgs& ep, float* ws,
                      size_t ws_floats, hipStream_t s) {
-  auto run = [&](auto launch) {
-    launch(a_kcontig, b_kcontig, A, lda, B, ldb, M, N, K, ep, ws, ws_floats, s);
-  };
+  auto run = [&](auto launch) { launch(A, lda, B, ldb, M, N, K, ep, ws, ws_floats, s); };
   const bool gt = ep.gelu_tanh != 0;
   switch (epi) {
-    case Epi::StoreF32: run(launch_epi<Epi::StoreF32, true>); break;
+    case Epi::StoreF32: run(launch_layout<false, false, Epi::StoreF32, true>); break;
     case Epi::BiasGelu:
-      if (gt) run(launch_epi<Epi::BiasGelu, true>);
-      else run(launch_epi<Epi::BiasGelu, false>);
+      if (gt) run(launch_layout<true, true, Epi::BiasGelu, true>);
+      else run(launch_layout<true, true, Epi::BiasGelu, false>);
       break;
-    case Epi::BiasResid: run(launch_epi<Epi::BiasResid, true>); break;
+    case Epi::BiasResid: run(launch_layout<true, true, Epi::BiasResid, true>); break;
     case Epi::DgeluSplit:
-      if (gt) run(launch_epi<Epi::DgeluSplit, true>);
-      else run(launch_epi<Epi::DgeluSplit, false>);
+      if (b_kcontig) run(launch_layout<true, true, Epi::DgeluSplit, true>);  // plain stores
+      else if (gt) run(launch_layout<true, false, Epi::DgeluSplit, true>);
+      else run(launch_layout<true, false, Epi::DgeluSplit, false>);
       break;
-    case Epi::LnGrad: run(launch_epi<Epi::LnGrad, true>); break;
+    case Epi::LnGrad: run(launch_layout<true, false, Epi::LnGrad, true>); break;
   }
 }
 

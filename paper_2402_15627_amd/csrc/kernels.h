@@ -144,8 +144,8 @@ inline int ln_row_groups(int n) { return (n + 63) / 64; }
 // Tail split: the first n_full tiles (a whole number of 256-tile waves) are
 // computed whole; each of the last `tail` tiles is split into `splits`
 // K-slices whose fp32 partial tiles go to a workspace and are summed in slice
-// order by a second kernel that applies the epilogue.  Only for the bf16
-// LDS-DMA path (K a multiple of 64); {tiles, 0, 1} means no split.
+// order by a second kernel that applies the epilogue.  bf16; {tiles, 0, 1}
+// means no split.
 struct SplitPlan {
   int n_full, tail, splits;
 };
