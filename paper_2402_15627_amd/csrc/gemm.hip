@@ -895,6 +895,36 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_dma_pair(DmaGemm g1, in
                                   g2.K / kBK, tiles2, 1, nullptr);
 }
 
+// The shared launch with every tile of the first GEMM cut into `splits`
+// K-slices, whose partial tiles splitk_reduce sums and finishes: a first GEMM of
+// few tiles and a long K would otherwise hold a handful of CUs long after the
+// second one's tiles are done (gemm_pair_splits).
+template <bool AK1, bool BK1, bool AK2, bool BK2>
+__global__ __launch_bounds__(kThreads, 1) void gemm_bf16_dma_pair_split(DmaGemm g1, int tiles1,
+                                                                        int splits,
+                                                                        float* __restrict__ part,
+                                                                        DmaGemm g2, int tiles2) {
+  const int b = (int)blockIdx.x, n1 = tiles1 * splits;
+  if (b < n1) {
+    const int j = xcd_remap(b, n1), nk = g1.K / kBK, chunk = (nk + splits - 1) / splits;
+    const int kt0 = min(nk, j % splits * chunk);
+    dma_gemm_item<AK1, BK1, Epi::StoreF32, true>(g1.A, g1.lda, g1.B, g1.ldb, g1.M, g1.N, g1.ep,
+                                                 j / splits, j % splits, kt0, min(nk, kt0 + chunk),
+                                                 0, splits, part);
+    return;
+  }
+  const int lid = xcd_remap(b - n1, tiles2);
+  int tm, tn;
+  tile_of<tile_group(Epi::StoreF32)>(lid, (g2.M + kBM - 1) / kBM, (g2.N + kBN - 1) / kBN, tm, tn);
+  if (g2.ep.rowsum && tn == 0)
+    dma_gemm_item<AK2, BK2, Epi::StoreF32, true, true>(g2.A, g2.lda, g2.B, g2.ldb, g2.M, g2.N,
+                                                       g2.ep, lid, -1, 0, g2.K / kBK, tiles2, 1,
+                                                       nullptr);
+  else
+    dma_gemm_item<AK2, BK2, Epi::StoreF32, true>(g2.A, g2.lda, g2.B, g2.ldb, g2.M, g2.N, g2.ep,
+                                                 lid, -1, 0, g2.K / kBK, tiles2, 1, nullptr);
+}
+
 // Persistent form of the pair launch: one workgroup per CU takes work items
 // until none is left.  The items (the first GEMM's tiles, then the
 // second's) are dealt to eight queues, one per XCD, each holding the tiles
@@ -1130,6 +1160,10 @@ GemmLaunch gemm_launch_of(Dt dt, int M, int N, int K) {
   return g;
 }
 
+static int tiles_of(const GemmSpec& g) {
+  return ((g.M + kBM - 1) / kBM) * ((g.N + kBN - 1) / kBN);
+}
+
 bool gemm_pair_supported(Dt dt, const GemmSpec& g1, const GemmSpec& g2) {
   if (dt != Dt::BF16) return false;
   for (const GemmSpec* g : {&g1, &g2})
@@ -1146,17 +1180,61 @@ void launch_queue_reset(int* queue, int n, hipStream_t s) {
   if (n > 0) queue_reset_kernel<<<1, 64, 0, s>>>(queue, n);
 }
 
-bool launch_gemm_pair(Dt dt, const GemmSpec& g1, const GemmSpec& g2, int* queue, hipStream_t s) {
+// Estimated end of the shared launch, in K-tile steps of one workgroup: n1
+// items of a steps and n2 of b on 256 CUs, the first started first; then, when
+// split, the sum of the slices (a launch, and the fp32 partial tiles written
+// and read back, about 1/16 of a step each).  Measured, backward of a block,
+// whole -> split tiles: 128 tokens, hidden 1024, FFN 4096 205 -> 72 us; 512,
+// 2048, 8192 367 -> 190 us; 1024, 4096, 16384 1059 -> 832 us; the serial block
+// of 2048 tokens, hidden 12288, 16 heads of 96 (dO + dW_o: 48 tiles of 192
+// K-tiles beside 288 of 32) 2675 -> 2609 us for the whole step.  2048 tokens
+// at hidden 4096 and above stay whole.
+int gemm_pair_splits(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats) {
+  const int t1 = tiles_of(g1), t2 = tiles_of(g2), nk1 = g1.K / kBK, nk2 = g2.K / kBK;
+  auto cost = [&](int s) {
+    const int n1 = t1 * s, a = (nk1 + s - 1) / s;
+    const double rounds = (double)((n1 + kCUs - 1) / kCUs) * a;
+    const double all = ((double)n1 * a + (double)t2 * nk2) / kCUs;
+    const double end = n1 + t2 <= kCUs ? std::max(a, nk2)
+                                       : std::max(rounds, all + 0.5 * std::min(a, nk2));
+    return s == 1 ? end : end + 4.0 + n1 / 16.0;
+  };
+  int best = 1;
+  for (int s = 2; s <= std::min(16, nk1); ++s)
+    if ((size_t)t1 * s * kBM * kBN <= ws_floats && cost(s) < cost(best)) best = s;
+  return best;
+}
+
+size_t gemm_pair_split_floats(Dt dt, const GemmSpec& g1, const GemmSpec& g2) {
+  if (!gemm_pair_supported(dt, g1, g2)) return 0;
+  const int s = gemm_pair_splits(g1, g2, SIZE_MAX);
+  return s > 1 ? (size_t)tiles_of(g1) * s * kBM * kBN : 0;
+}
+
+bool launch_gemm_pair(Dt dt, const GemmSpec& g1, const GemmSpec& g2, int* queue, float* split_ws,
+                      size_t split_ws_floats, hipStream_t s) {
   if (!gemm_pair_supported(dt, g1, g2)) return false;
   auto desc = [](const GemmSpec& g) {
     return DmaGemm{(const bf16*)g.A, g.lda, (const bf16*)g.B, g.ldb, g.M, g.N, g.K, g.ep};
   };
-  auto tiles = [](const GemmSpec& g) {
-    return ((g.M + kBM - 1) / kBM) * ((g.N + kBN - 1) / kBN);
-  };
   const DmaGemm d1 = desc(g1), d2 = desc(g2);
-  const int t1 = tiles(g1), t2 = tiles(g2);
+  const int t1 = tiles_of(g1), t2 = tiles_of(g2);
   const size_t lds = 4 * (size_t)kTileBytes;
+  const int splits = split_ws ? gemm_pair_splits(g1, g2, split_ws_floats) : 1;
+  if (splits > 1) {
+    gemm_bf16_dma_pair_split<true, false, false, false>
+        <<<t1 * splits + t2, kThreads, lds, s>>>(d1, t1, splits, split_ws, d2, t2);
+    static_assert(tile_group(Epi::StoreF32) == tile_group(Epi::LnGrad) &&
+                      tile_group(Epi::StoreF32) == tile_group(Epi::DgeluSplit),
+                  "the slices and their sum walk the tiles alike");
+    auto reduce = [&](auto kernel) {
+      kernel<<<t1 * 64, 256, 0, s>>>(split_ws, g1.M, g1.N, 0, splits, g1.ep);
+    };
+    if (g1.epi == Epi::LnGrad) reduce(splitk_reduce<Epi::LnGrad, true>);
+    else if (g1.ep.gelu_tanh) reduce(splitk_reduce<Epi::DgeluSplit, true>);
+    else reduce(splitk_reduce<Epi::DgeluSplit, false>);
+    return true;
+  }
   // (the erf GeLU' form keeps the plain launch: its persistent build spills)
   if (queue && (g1.epi == Epi::LnGrad || g1.ep.gelu_tanh)) {
     const PairArgs pa{d1, t1, d2, t2, queue};

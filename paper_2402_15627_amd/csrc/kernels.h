@@ -172,9 +172,11 @@ void launch_gemm(Dt dt, Epi epi, bool a_kcontig, bool b_kcontig, const void* A, 
                  const void* B, int ldb, int M, int N, int K, const EpiArgs& ep, float* split_ws,
                  size_t split_ws_floats, hipStream_t s);
 
-// Two independent GEMMs in one launch, neither split along K: the first
-// one's tiles are started first (give it the longer K), and the second one's
-// tiles fill the CUs the first leaves idle.  Supported: bf16, K multiples of
+// Two independent GEMMs in one launch: the first one's tiles are started first
+// (give it the longer K), and the second one's tiles fill the CUs the first
+// leaves idle.  Where the first one's few long tiles would outlast the launch
+// they are split along K (gemm_pair_splits), as launch_gemm splits, and a
+// second kernel sums the slices.  Supported: bf16, K multiples of
 // 64 and operands the LDS-DMA path takes, with the first GEMM A K-contiguous,
 // B MN-contiguous and a DgeluSplit or LnGrad epilogue, the second both
 // MN-contiguous with StoreF32 (the backward pass's dC + dW_out and
@@ -191,7 +193,7 @@ struct GemmSpec {
   EpiArgs ep;
 };
 //
-// With queue non-NULL the launch is persistent: one workgroup per CU takes
+// With queue non-NULL an unsplit launch is persistent: one workgroup per CU takes
 // tiles from per-XCD queues until none is left, so XCDs that run slower hand
 // their last tiles to the others.  queue points to kQueueInts ints (device
 // memory) that must be zero when the launch runs, e.g. from
@@ -201,7 +203,13 @@ struct GemmSpec {
 constexpr int kQueueInts = 8;
 void launch_queue_reset(int* queue, int n, hipStream_t s);  // n ints = 0 (a kernel)
 bool gemm_pair_supported(Dt dt, const GemmSpec& g1, const GemmSpec& g2);
-bool launch_gemm_pair(Dt dt, const GemmSpec& g1, const GemmSpec& g2, int* queue, hipStream_t s);
+// K-slices per tile of the first GEMM in the shared launch of a supported pair,
+// given ws_floats of space for partial tiles (1: whole tiles, and the first
+// GEMM's epilogue forms delta when asked to; a split launch does not).
+int gemm_pair_splits(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats);
+size_t gemm_pair_split_floats(Dt dt, const GemmSpec& g1, const GemmSpec& g2);
+bool launch_gemm_pair(Dt dt, const GemmSpec& g1, const GemmSpec& g2, int* queue, float* split_ws,
+                      size_t split_ws_floats, hipStream_t s);
 
 // -------------------------------------------------------------- attention
 // Causal sliding-window attention over [batch, seq] rows; q/k/v/o/do/dq/dk/dv

@@ -128,6 +128,70 @@ SavedLayout saved_layout(const Dims& d) {
   return L;
 }
 
+// Element offset helper for activation buffers.
+const void* at(const void* base, long long elems, size_t esz) {
+  return (const char*)base + (size_t)elems * esz;
+}
+void* at(void* base, long long elems, size_t esz) { return (char*)base + (size_t)elems * esz; }
+
+// The GEMMs of the backward passes that may share a launch, built in one
+// place for the launches and for pblock_backward_pairs, so that the query
+// reports the pairing the launches make.  Null operands and default epilogue
+// arguments describe the shapes alone.
+struct ParallelBwdGemms {
+  pb::GemmSpec dc, dw_out, dh, dw_in;
+};
+ParallelBwdGemms parallel_bwd_gemms(const Dims& d, const void* dy, const void* w_out,
+                                    const void* c, const void* dz, const void* w_in,
+                                    const void* h, const pb::EpiArgs& e_dc,
+                                    const pb::EpiArgs& e_dwo, const pb::EpiArgs& e_dh,
+                                    const pb::EpiArgs& e_dwi) {
+  const int T = (int)d.T, H = (int)d.H, N_in = (int)d.N_in, K_out = (int)d.K_out;
+  return {
+      // dC = dy W_out (B MN-contiguous)
+      {pb::Epi::DgeluSplit, true, false, dy, H, w_out, K_out, T, K_out, H, e_dc},
+      // dW_out = dy^T C (contraction over tokens)
+      {pb::Epi::StoreF32, false, false, dy, H, c, K_out, H, K_out, T, e_dwo},
+      // dh = dZ W_in
+      {pb::Epi::LnGrad, true, false, dz, N_in, w_in, H, T, H, N_in, e_dh},
+      // dW_in = dZ^T h
+      {pb::Epi::StoreF32, false, false, dz, N_in, h, H, N_in, H, T, e_dwi}};
+}
+
+struct SerialBwdGemms {
+  pb::GemmSpec dg, dw_down, dh2, dw_up, d_o, dw_o, dh1, dw_qkv;
+};
+struct SerialBwdOperands {
+  const void *dy, *dx1, *c, *dz, *h1, *h2, *w_in, *w_out;
+};
+SerialBwdGemms serial_bwd_gemms(const Dims& d, const SerialBwdOperands& o,
+                                const pb::EpiArgs& e_dg, const pb::EpiArgs& e_wd,
+                                const pb::EpiArgs& e_dh2, const pb::EpiArgs& e_wu,
+                                const pb::EpiArgs& e_do, const pb::EpiArgs& e_wo,
+                                const pb::EpiArgs& e_dh1, const pb::EpiArgs& e_wq) {
+  const int T = (int)d.T, H = (int)d.H, A = (int)d.A, F = (int)d.F, N_in = (int)d.N_in,
+            K_out = (int)d.K_out;
+  const size_t e = d.esz;
+  auto off = [&](const void* p, long long n) { return p ? at(p, n, e) : nullptr; };
+  return {
+      // dG = dy W_down
+      {pb::Epi::DgeluSplit, true, false, o.dy, H, off(o.w_out, A), K_out, T, F, H, e_dg},
+      // dW_down = dy^T G
+      {pb::Epi::StoreF32, false, false, o.dy, H, off(o.c, A), K_out, H, F, T, e_wd},
+      // dh2 = dU W_up
+      {pb::Epi::LnGrad, true, false, off(o.dz, 3LL * A), N_in, off(o.w_in, 3LL * A * H), H, T, H,
+       F, e_dh2},
+      // dW_up = dU^T h2
+      {pb::Epi::StoreF32, false, false, off(o.dz, 3LL * A), N_in, o.h2, H, F, H, T, e_wu},
+      // dO = dx1 W_o
+      {pb::Epi::DgeluSplit, true, false, o.dx1, H, o.w_out, K_out, T, A, H, e_do},
+      // dW_o = dx1^T O
+      {pb::Epi::StoreF32, false, false, o.dx1, H, o.c, K_out, H, A, T, e_wo},
+      // dh1 = dQKV W_qkv
+      {pb::Epi::LnGrad, true, false, o.dz, N_in, o.w_in, H, T, H, 3 * A, e_dh1},
+      // dW_qkv = dQKV^T h1
+      {pb::Epi::StoreF32, false, false, o.dz, N_in, o.h1, H, 3 * A, H, T, e_wq}};
+}
 // Optional space for split work: the GEMMs' tail-split partial tiles and the
 // attention kernels' chunk partials.  They are never live at the same time,
 // so one region serves both.
@@ -140,7 +204,12 @@ size_t split_bytes_fwd(const Dims& d, pb::Dt dt) {
 }
 size_t split_bytes_bwd(const Dims& d, pb::Dt dt) {
   const int T = (int)d.T, H = (int)d.H, N_in = (int)d.N_in, K_out = (int)d.K_out;
-  size_t m = pb::gemm_split_floats(dt, T, K_out, H);
+  const pb::EpiArgs none;
+  const ParallelBwdGemms g = parallel_bwd_gemms(d, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                                nullptr, none, none, none, none);
+  size_t m = std::max(pb::gemm_pair_split_floats(dt, g.dc, g.dw_out),
+                      pb::gemm_pair_split_floats(dt, g.dh, g.dw_in));
+  m = std::max(m, pb::gemm_split_floats(dt, T, K_out, H));
   m = std::max(m, pb::gemm_split_floats(dt, H, K_out, T));
   m = std::max(m, pb::gemm_split_floats(dt, T, H, N_in));
   m = std::max(m, pb::gemm_split_floats(dt, N_in, H, T));
@@ -225,6 +294,14 @@ size_t serial_split_bwd(const Dims& d, pb::Dt dt) {
   const int T = (int)d.T, H = (int)d.H, A = (int)d.A, F = (int)d.F;
   size_t m = max_split_bytes(dt, {{T, F, H}, {H, F, T}, {T, H, F}, {F, H, T}, {T, A, H},
                                   {H, A, T}, {T, H, 3 * A}, {3 * A, H, T}});
+  const pb::EpiArgs none;
+  const SerialBwdGemms g =
+      serial_bwd_gemms(d, SerialBwdOperands{}, none, none, none, none, none, none, none, none);
+  for (size_t f : {pb::gemm_pair_split_floats(dt, g.dg, g.dw_down),
+                   pb::gemm_pair_split_floats(dt, g.dh2, g.dw_up),
+                   pb::gemm_pair_split_floats(dt, g.d_o, g.dw_o),
+                   pb::gemm_pair_split_floats(dt, g.dh1, g.dw_qkv)})
+    m = std::max(m, f * 4);
   const pb::AttnShape a = attn_shape(d);
   return std::max(m, pb::attn_bwd_partial_bytes(a, pb::attn_bwd_split_plan(dt, a)));
 }
@@ -283,12 +360,6 @@ pb_status finish_launches() {
 }
 
 pb::Dt dt_of(const pb_config* c) { return c->dtype == PB_BF16 ? pb::Dt::BF16 : pb::Dt::F32; }
-
-// Element offset helper for activation buffers.
-const void* at(const void* base, long long elems, size_t esz) {
-  return (const char*)base + (size_t)elems * esz;
-}
-void* at(void* base, long long elems, size_t esz) { return (char*)base + (size_t)elems * esz; }
 
 pb_status check_attn_config(const pb_config* c) {
   if (!c) return fail(PB_ERR_INVALID_ARG, "cfg is NULL");
@@ -454,67 +525,6 @@ pb_status pblock_forward_timed(const pb_config* cfg, const void* x, const void* 
   return finish_launches();
 }
 
-namespace {
-// The GEMMs of the backward passes that may share a launch, built in one
-// place for the launches and for pblock_backward_pairs, so that the query
-// reports the pairing the launches make.  Null operands and default epilogue
-// arguments describe the shapes alone.
-struct ParallelBwdGemms {
-  pb::GemmSpec dc, dw_out, dh, dw_in;
-};
-ParallelBwdGemms parallel_bwd_gemms(const Dims& d, const void* dy, const void* w_out,
-                                    const void* c, const void* dz, const void* w_in,
-                                    const void* h, const pb::EpiArgs& e_dc,
-                                    const pb::EpiArgs& e_dwo, const pb::EpiArgs& e_dh,
-                                    const pb::EpiArgs& e_dwi) {
-  const int T = (int)d.T, H = (int)d.H, N_in = (int)d.N_in, K_out = (int)d.K_out;
-  return {
-      // dC = dy W_out (B MN-contiguous)
-      {pb::Epi::DgeluSplit, true, false, dy, H, w_out, K_out, T, K_out, H, e_dc},
-      // dW_out = dy^T C (contraction over tokens)
-      {pb::Epi::StoreF32, false, false, dy, H, c, K_out, H, K_out, T, e_dwo},
-      // dh = dZ W_in
-      {pb::Epi::LnGrad, true, false, dz, N_in, w_in, H, T, H, N_in, e_dh},
-      // dW_in = dZ^T h
-      {pb::Epi::StoreF32, false, false, dz, N_in, h, H, N_in, H, T, e_dwi}};
-}
-
-struct SerialBwdGemms {
-  pb::GemmSpec dg, dw_down, dh2, dw_up, d_o, dw_o, dh1, dw_qkv;
-};
-struct SerialBwdOperands {
-  const void *dy, *dx1, *c, *dz, *h1, *h2, *w_in, *w_out;
-};
-SerialBwdGemms serial_bwd_gemms(const Dims& d, const SerialBwdOperands& o,
-                                const pb::EpiArgs& e_dg, const pb::EpiArgs& e_wd,
-                                const pb::EpiArgs& e_dh2, const pb::EpiArgs& e_wu,
-                                const pb::EpiArgs& e_do, const pb::EpiArgs& e_wo,
-                                const pb::EpiArgs& e_dh1, const pb::EpiArgs& e_wq) {
-  const int T = (int)d.T, H = (int)d.H, A = (int)d.A, F = (int)d.F, N_in = (int)d.N_in,
-            K_out = (int)d.K_out;
-  const size_t e = d.esz;
-  auto off = [&](const void* p, long long n) { return p ? at(p, n, e) : nullptr; };
-  return {
-      // dG = dy W_down
-      {pb::Epi::DgeluSplit, true, false, o.dy, H, off(o.w_out, A), K_out, T, F, H, e_dg},
-      // dW_down = dy^T G
-      {pb::Epi::StoreF32, false, false, o.dy, H, off(o.c, A), K_out, H, F, T, e_wd},
-      // dh2 = dU W_up
-      {pb::Epi::LnGrad, true, false, off(o.dz, 3LL * A), N_in, off(o.w_in, 3LL * A * H), H, T, H,
-       F, e_dh2},
-      // dW_up = dU^T h2
-      {pb::Epi::StoreF32, false, false, off(o.dz, 3LL * A), N_in, o.h2, H, F, H, T, e_wu},
-      // dO = dx1 W_o
-      {pb::Epi::DgeluSplit, true, false, o.dx1, H, o.w_out, K_out, T, A, H, e_do},
-      // dW_o = dx1^T O
-      {pb::Epi::StoreF32, false, false, o.dx1, H, o.c, K_out, H, A, T, e_wo},
-      // dh1 = dQKV W_qkv
-      {pb::Epi::LnGrad, true, false, o.dz, N_in, o.w_in, H, T, H, 3 * A, e_dh1},
-      // dW_qkv = dQKV^T h1
-      {pb::Epi::StoreF32, false, false, o.dz, N_in, o.h1, H, 3 * A, H, T, e_wq}};
-}
-}  // namespace
-
 pb_status pblock_gemm_plan(pb_dtype dtype, int M, int N, int K, pb_gemm_plan* plan) {
   if (!plan) return fail(PB_ERR_INVALID_ARG, "plan is NULL");
   if (dtype != PB_BF16 && dtype != PB_F32) return fail(PB_ERR_INVALID_ARG, "unknown dtype");
@@ -665,10 +675,12 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x, const void*
   // leaves the accumulators, instead of re-reading dO and O in a launch of
   // their own: heads of 64 or 128 columns whose blocks align with the
   // epilogue's 128-column wave blocks.
-  const bool delta_in_dc = pair_out && (d.d == 64 || d.d == 128) && A % 128 == 0;
+  const bool whole_out = pair_out && pb::gemm_pair_splits(g_dc, g_dwo, split_f) == 1;
+  const bool delta_in_dc = whole_out && (d.d == 64 || d.d == 128) && A % 128 == 0;
   // db_in = sum over tokens of dZ: the row sums of dW_in's A operand (dZ^T),
   // formed by the shared launch's first tile column of dW_in
   const bool pair_in = pb::gemm_pair_supported(dt, g_dh, g_dwi);
+  const bool whole_in = pair_in && pb::gemm_pair_splits(g_dh, g_dwi, split_f) == 1;
   if (pair_in) G.dw_in.ep.rowsum = db_in;
   if (delta_in_dc) {
     G.dc.ep.o_rows = c;  // O = C[:, :A]
@@ -680,10 +692,10 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x, const void*
   }
   {
     StepScope sc(step_ev, PB_STEP_DC, stream);  // with dW_out when they share a launch
-    // the shared launches are persistent: their queue heads start at zero
-    if (pair_out || pair_in) pb::launch_queue_reset(queue, 2 * pb::kQueueInts, stream);
+    // shared launches of whole tiles are persistent: their queue heads start at zero
+    if (whole_out || whole_in) pb::launch_queue_reset(queue, 2 * pb::kQueueInts, stream);
     if (pair_out)
-      pb::launch_gemm_pair(dt, g_dc, g_dwo, queue, stream);
+      pb::launch_gemm_pair(dt, g_dc, g_dwo, queue, split_ws, split_f, stream);
     else
       run(g_dc);
   }
@@ -700,7 +712,7 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x, const void*
   {
     StepScope sc(step_ev, PB_STEP_DH, stream);  // with dW_in when they share a launch
     if (pair_in)
-      pb::launch_gemm_pair(dt, g_dh, g_dwi, queue + pb::kQueueInts, stream);
+      pb::launch_gemm_pair(dt, g_dh, g_dwi, queue + pb::kQueueInts, split_ws, split_f, stream);
     else
       run(g_dh);
   }
@@ -1140,6 +1152,7 @@ pb_status pblock_serial_backward(const pb_config* cfg, const void* x, const void
     G.dw_qkv.ep.rowsum = db_in;
   }
   const bool delta_in_do = pb::gemm_pair_supported(dt, G.d_o, G.dw_o) &&
+                           pb::gemm_pair_splits(G.d_o, G.dw_o, split_f) == 1 &&
                            (d.d == 64 || d.d == 128) && A % 128 == 0;
   if (delta_in_do) {
     G.d_o.ep.o_rows = c;  // O = C[:, :A]
@@ -1155,15 +1168,19 @@ pb_status pblock_serial_backward(const pb_config* cfg, const void* x, const void
   };
   const pb::GemmSpec* deferred[4];
   int n_deferred = 0;
-  // the shared launches are persistent, each with its own queue heads,
-  // zeroed here
+  // shared launches of whole tiles are persistent, each with its own queue
+  // heads, zeroed here
   static_assert(kBwdQueueSets >= 4, "one queue per shared launch");
-  if (pb::gemm_pair_supported(dt, G.dg, G.dw_down) || pb::gemm_pair_supported(dt, G.dh2, G.dw_up) ||
-      pb::gemm_pair_supported(dt, G.d_o, G.dw_o) || pb::gemm_pair_supported(dt, G.dh1, G.dw_qkv))
+  auto whole_pair = [&](const pb::GemmSpec& g, const pb::GemmSpec& wg) {
+    return pb::gemm_pair_supported(dt, g, wg) && pb::gemm_pair_splits(g, wg, split_f) == 1;
+  };
+  if (whole_pair(G.dg, G.dw_down) || whole_pair(G.dh2, G.dw_up) || whole_pair(G.d_o, G.dw_o) ||
+      whole_pair(G.dh1, G.dw_qkv))
     pb::launch_queue_reset(queue, 4 * pb::kQueueInts, stream);
   int n_pairs = 0;
   auto run_with = [&](const pb::GemmSpec& g, const pb::GemmSpec& wg) {
-    if (!pb::launch_gemm_pair(dt, g, wg, queue + pb::kQueueInts * n_pairs++, stream)) {
+    if (!pb::launch_gemm_pair(dt, g, wg, queue + pb::kQueueInts * n_pairs++, split_ws, split_f,
+                              stream)) {
       run(g);
       deferred[n_deferred++] = &wg;
     }
