@@ -456,6 +456,14 @@ PB_DEV void wave_epilogue_lds(const EpiArgs& ep, float* __restrict__ part_tile,
         rs_l = ep.rstd[mr];
       }
     }
+    int dl_b = 0, dl_next = 0, dl_head = 0;
+    if constexpr (EPI == Epi::DgeluSplit) {
+      if (!part_tile && ep.delta) {
+        dl_b = m0h / ep.delta_seq;
+        dl_next = (dl_b + 1) * ep.delta_seq;
+        dl_head = ep.delta_hd == 128 ? n >> 7 : n >> 6;
+      }
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
@@ -480,7 +488,7 @@ PB_DEV void wave_epilogue_lds(const EpiArgs& ep, float* __restrict__ part_tile,
           if (n >= ep.split) {
             float g[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) g[e] = gelu<GT>(o[e]);
+            for (int e = 0; e < 4; ++e) g[e] = gelu<bf16, GT>(o[e]);
             store4((bf16*)ep.out2 + (size_t)m * ep.ld_out2 + (n - ep.split) + ep.col2, g);
           }
         }
@@ -504,17 +512,20 @@ PB_DEV void wave_epilogue_lds(const EpiArgs& ep, float* __restrict__ part_tile,
 #pragma unroll
             for (int e = 0; e < 4; ++e) sd += bf2f(f2bf(v[e])) * ov[e];
             const int gl = ep.delta_hd >> 2;  // lanes per head: 32 or 16
-            for (int off = 1; off < gl; off <<= 1) sd += __shfl_xor(sd, off, 64);
+            sd = row16_sum(sd);
+            if (gl == 32) sd = swap16_sum(sd);
             if ((c & (gl - 1)) == 0 && ok) {
-              const int b = m / ep.delta_seq, tt = m - b * ep.delta_seq;
-              ep.delta[((size_t)b * ep.delta_heads + n / ep.delta_hd) * ep.delta_seq + tt] = sd;
+              // batch row of m: the half's rows span at most two of 32 or more tokens
+              const int b = ep.delta_seq >= 32 ? dl_b + (m >= dl_next) : m / ep.delta_seq;
+              ep.delta[((size_t)b * ep.delta_heads + dl_head) * ep.delta_seq +
+                       (m - b * ep.delta_seq)] = sd;
             }
           }
         } else {
           const float u[4] = {lo_bf(in2[t][0]), hi_bf(in2[t][0]), lo_bf(in2[t][1]),
                               hi_bf(in2[t][1])};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = v[e] * gelu_grad<GT>(u[e]);
+          for (int e = 0; e < 4; ++e) o[e] = v[e] * gelu_grad<bf16, GT>(u[e]);
           if (ok)
             store4((bf16*)ep.out2 + (size_t)m * ep.ld_out2 + (n - ep.split) + ep.col2, o);
         }
@@ -539,11 +550,8 @@ PB_DEV void wave_epilogue_lds(const EpiArgs& ep, float* __restrict__ part_tile,
             s2 += g * ((xv[e] - mu) * rs);
           }
         }
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) {
-          s1 += __shfl_xor(s1, off, 64);
-          s2 += __shfl_xor(s2, off, 64);
-        }
+        s1 = row16_sum(s1);
+        s2 = row16_sum(s2);
         if ((c & 15) == 0 && ok)  // n is the group's first column
           ep.rowpart[(size_t)m * ep.rowpart_ld + n / 64] = make_float2(s1, s2);
       }
@@ -1067,11 +1075,8 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float* __restrict__ p
     // a wave is one row of the tile; 16 lanes cover one 64-column group
     float s1 = 0.f, s2 = 0.f;
     if (ok) ln_terms4<bf16>(ep, m, n, v, ep.mean[m], ep.rstd[m], s1, s2);
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) {
-      s1 += __shfl_xor(s1, off, 16);
-      s2 += __shfl_xor(s2, off, 16);
-    }
+    s1 = row16_sum(s1);
+    s2 = row16_sum(s2);
     if ((threadIdx.x & 15) == 0 && ok)
       ep.rowpart[(size_t)m * ep.rowpart_ld + n / 64] = make_float2(s1, s2);
   }

@@ -27,7 +27,7 @@ PB_DEV void epi_store4(const EpiArgs& ep, int m, int n, const float* v) {
     if (n >= ep.split) {
       float g[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) g[e] = gelu<GT>(z[e]);
+      for (int e = 0; e < 4; ++e) g[e] = gelu<T, GT>(z[e]);
       store4((T*)ep.out2 + (size_t)m * ep.ld_out2 + (n - ep.split) + ep.col2, g);
     }
   } else if constexpr (EPI == Epi::BiasResid) {
@@ -45,7 +45,7 @@ PB_DEV void epi_store4(const EpiArgs& ep, int m, int n, const float* v) {
       float u[4], o[4];
       load4((const T*)ep.aux + off, u);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = v[e] * gelu_grad<GT>(u[e]);
+      for (int e = 0; e < 4; ++e) o[e] = v[e] * gelu_grad<T, GT>(u[e]);
       store4((T*)ep.out2 + off, o);
     }
   }

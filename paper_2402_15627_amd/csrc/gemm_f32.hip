@@ -350,11 +350,8 @@ __global__ __launch_bounds__(kSThreads) void gemm_f32_waves_kernel(
   if constexpr (EPI == Epi::LnGrad) {
     float s1 = 0.f, s2 = 0.f;
     if (ok) ln_terms4<float>(ep, m, c, v, ep.mean[m], ep.rstd[m], s1, s2);
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) {
-      s1 += __shfl_xor(s1, off, 16);
-      s2 += __shfl_xor(s2, off, 16);
-    }
+    s1 = row16_sum(s1);
+    s2 = row16_sum(s2);
     if (c4 == 0 && m < M) ep.rowpart[(size_t)m * ep.rowpart_ld + n0 / 64] = make_float2(s1, s2);
   }
 }
@@ -382,11 +379,8 @@ __global__ __launch_bounds__(256) void f32_splitk_reduce(const float* __restrict
   if constexpr (EPI == Epi::LnGrad) {
     float s1 = 0.f, s2 = 0.f;
     if (ok) ln_terms4<float>(ep, m, c, v, ep.mean[m], ep.rstd[m], s1, s2);
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) {
-      s1 += __shfl_xor(s1, off, 16);
-      s2 += __shfl_xor(s2, off, 16);
-    }
+    s1 = row16_sum(s1);
+    s2 = row16_sum(s2);
     if ((threadIdx.x & 15) == 0) ep.rowpart[(size_t)m * ep.rowpart_ld + grp] = make_float2(s1, s2);
   }
 }
