@@ -862,6 +862,17 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_dma_kernel(const bf16* 
     kt1 = min(nk_all, kt0 + chunk);
   }
   const int left = RK && kt1 == nk_all ? K - (nk_all - 1) * kBK : kDK;
+  if constexpr (EPI == Epi::StoreF32) {
+    // the row sums of A, when asked for (unsplit launches), from the first
+    // tile column
+    int tm, tn;
+    tile_of<tile_group(EPI)>(lid, tiles_m, tiles_n, tm, tn);
+    if (ep.rowsum && tn == 0) {
+      dma_gemm_item<AK, BK, EPI, GT, true, RK>(A, lda, B, ldb, M, N, ep, lid, slice, kt0, kt1,
+                                               n_full, splits, part, nullptr, nullptr, -1, left);
+      return;
+    }
+  }
   dma_gemm_item<AK, BK, EPI, GT, false, RK>(A, lda, B, ldb, M, N, ep, lid, slice, kt0, kt1, n_full,
                                             splits, part, nullptr, nullptr, -1, left);
 }
@@ -1163,6 +1174,14 @@ GemmLaunch gemm_launch_of(Dt dt, int M, int N, int K) {
     g = gemm_f32_launch_of(M, N, K);
   }
   return g;
+}
+
+bool gemm_rowsum_supported(Dt dt, const GemmSpec& g, size_t ws_floats) {
+  if (dt != Dt::BF16 || g.epi != Epi::StoreF32 ||
+      !dma_offsets_fit(g.a_kcontig, g.lda, g.b_kcontig, g.ldb))
+    return false;
+  const size_t split = gemm_split_floats(dt, g.M, g.N, g.K);
+  return split == 0 || ws_floats < split;  // launched unsplit
 }
 
 static int tiles_of(const GemmSpec& g) {

@@ -135,8 +135,9 @@ struct EpiArgs {
   int ld_o_rows = 0;
   float* delta = nullptr;
   int delta_seq = 0, delta_heads = 0, delta_hd = 0;
-  // StoreF32 as the second GEMM of launch_gemm_pair only: when set, also
-  // rowsum[m] = sum over k of A(m, k) (fp32), for every row m < M.
+  // StoreF32 as the second GEMM of launch_gemm_pair, or where
+  // gemm_rowsum_supported: when set, also rowsum[m] = sum over k of A(m, k)
+  // (fp32), for every row m < M.
   float* rowsum = nullptr;
 };
 // 64-column groups of the LnGrad row terms for a row of n columns.
@@ -203,6 +204,9 @@ struct GemmSpec {
 constexpr int kQueueInts = 8;
 void launch_queue_reset(int* queue, int n, hipStream_t s);  // n ints = 0 (a kernel)
 bool gemm_pair_supported(Dt dt, const GemmSpec& g1, const GemmSpec& g2);
+// Whether launch_gemm of a weight gradient, given ws_floats of split space,
+// forms rowsum.
+bool gemm_rowsum_supported(Dt dt, const GemmSpec& g, size_t ws_floats);
 // K-slices per tile of the first GEMM in the shared launch of a supported pair,
 // given ws_floats of space for partial tiles (1: whole tiles, and the first
 // GEMM's epilogue forms delta when asked to; a split launch does not).

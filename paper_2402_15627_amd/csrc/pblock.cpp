@@ -678,10 +678,11 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x, const void*
   const bool whole_out = pair_out && pb::gemm_pair_splits(g_dc, g_dwo, split_f) == 1;
   const bool delta_in_dc = whole_out && (d.d == 64 || d.d == 128) && A % 128 == 0;
   // db_in = sum over tokens of dZ: the row sums of dW_in's A operand (dZ^T),
-  // formed by the shared launch's first tile column of dW_in
+  // formed by the first tile column of dW_in, in the shared launch or alone
   const bool pair_in = pb::gemm_pair_supported(dt, g_dh, g_dwi);
   const bool whole_in = pair_in && pb::gemm_pair_splits(g_dh, g_dwi, split_f) == 1;
-  if (pair_in) G.dw_in.ep.rowsum = db_in;
+  const bool db_in_fused = pair_in || pb::gemm_rowsum_supported(dt, g_dwi, split_f);
+  if (db_in_fused) G.dw_in.ep.rowsum = db_in;
   if (delta_in_dc) {
     G.dc.ep.o_rows = c;  // O = C[:, :A]
     G.dc.ep.ld_o_rows = K_out;
@@ -729,11 +730,10 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x, const void*
   {
     StepScope sc(step_ev, PB_STEP_DB_OUT, stream);  // now inside the LN backward's column sums
   }
-  // db_in = sum over tokens of dZ (already formed in dW_in's launch when
-  // it shared dh's)
+  // db_in = sum over tokens of dZ, where dW_in's launch does not form it
   {
     StepScope sc(step_ev, PB_STEP_DB_IN, stream);
-    if (!pair_in) pb::launch_colsum(dt, dz, N_in, T, N_in, part, db_in, stream);
+    if (!db_in_fused) pb::launch_colsum(dt, dz, N_in, T, N_in, part, db_in, stream);
   }
   {
     StepScope sc(step_ev, PB_STEP_DW_OUT, stream);  // empty when it shared dC's launch
@@ -1143,10 +1143,12 @@ pb_status pblock_serial_backward(const pb_config* cfg, const void* x, const void
   SerialBwdGemms G = serial_bwd_gemms(
       d, SerialBwdOperands{dy, dx1, c, dz, h1, h2, w_in, w_out}, e1, wd, e2, wu, e3, wo, e4, wq);
   // As in the parallel block: db_in from the row sums of the weight
-  // gradients' A operands (dU^T in dW_up, dQKV^T in dW_qkv) when both share
-  // launches, and the attention backward's delta from the dO GEMM's epilogue
-  const bool db_in_fused = pb::gemm_pair_supported(dt, G.dh2, G.dw_up) &&
-                           pb::gemm_pair_supported(dt, G.dh1, G.dw_qkv);
+  // gradients' A operands (dU^T in dW_up, dQKV^T in dW_qkv) when both form
+  // them, and the attention backward's delta from the dO GEMM's epilogue
+  auto sums_rows = [&](const pb::GemmSpec& g, const pb::GemmSpec& wg) {
+    return pb::gemm_pair_supported(dt, g, wg) || pb::gemm_rowsum_supported(dt, wg, split_f);
+  };
+  const bool db_in_fused = sums_rows(G.dh2, G.dw_up) && sums_rows(G.dh1, G.dw_qkv);
   if (db_in_fused) {
     G.dw_up.ep.rowsum = db_in + 3LL * A;
     G.dw_qkv.ep.rowsum = db_in;
