@@ -1247,10 +1247,11 @@ void bwd_d(Dt dt, const AttnShape& a, const void* q, const void* k, const void* 
 constexpr long long kSplitBelow = 2048;
 constexpr long long kSplitTarget = 1536;
 
-AttnSplit attn_split_plan(Dt dt, const AttnShape& a) {
+// The split that the grids alone ask for.
+static AttnSplit grid_split_plan(Dt dt, const AttnShape& a) {
   AttnSplit p{kUnsplit, 1, kUnsplit, 1};
   if (dt != Dt::BF16) return p;
-  auto choose = [&](int block, int waves, bool keys, int& chunk, int& n) {
+  auto choose = [&](int block, int waves, bool keys, int& chunk, int& n, int& tiles) {
     const int nb = (a.seq + block - 1) / block;
     const long long w = (long long)nb * a.heads * a.batch * waves;
     if (w >= kSplitBelow) return;
@@ -1258,6 +1259,7 @@ AttnSplit attn_split_plan(Dt dt, const AttnShape& a) {
     for (int i = 0; i < nb; ++i)
       max_tiles = std::max(max_tiles, keys ? kblock_tiles(i * block, a.seq, a.window)
                                            : qblock_tiles(i * block, a.seq, a.window));
+    tiles = max_tiles;
     const int want = (int)((kSplitTarget + w - 1) / w);
     const int m = std::min(want, (max_tiles + 1) / 2);
     if (m < 2) return;
@@ -1265,18 +1267,47 @@ AttnSplit attn_split_plan(Dt dt, const AttnShape& a) {
     n = (max_tiles + chunk - 1) / chunk;
     if (n < 2) chunk = kUnsplit, n = 1;
   };
-  choose(kBlockQ, kWavesQ, false, p.fwd_chunk, p.fwd_n);
-  choose(kBlockK, kWavesK, true, p.kv_chunk, p.kv_n);
+  choose(kBlockQ, kWavesQ, false, p.fwd_chunk, p.fwd_n, p.fwd_tiles);
+  choose(kBlockK, kWavesK, true, p.kv_chunk, p.kv_n, p.kv_tiles);
   return p;
 }
 
+// A split pays where the time it takes off the longest block exceeds its merge:
+// a launch (about 5 us; two, 8 us, in the backward) and the fp32 partials
+// written and read back (about 10 TB/s, they stay in the caches).  A tile takes
+// about 0.9 us in the forward, 1.05 us for dK/dV and 2.1 for dQ.  Measured with
+// the split and without (us, forward | backward):
+//   2048 tokens, 12 heads of 128, full window   37 / 46   |
+//   4544, 3 x 128, full                         48 / 122  | 116 / 168
+//   1024, 8 x 128, full                         24 / 26   | 39 / 44
+//   512, 8 x 128, full                          14 / 16   | 30 / 26
+//   1024, 16 x 96, window 512                   22 / 17   | 45 / 29
+//   4096, 4 x 128, window 256                   23 / 15   | 48 / 28
+//   3 x 675, 16 x 128, window 300               25 / 18   |
+AttnSplit attn_split_plan(Dt dt, const AttnShape& a) {
+  AttnSplit p = grid_split_plan(dt, a);
+  const double merge_us = 5.0 + 2.0 * attn_fwd_partial_bytes(a, p) / 1e7;
+  if (p.fwd_n > 1 && 0.9 * (p.fwd_tiles - p.fwd_chunk) < merge_us)
+    p.fwd_chunk = kUnsplit, p.fwd_n = 1;
+  return p;
+}
+
+size_t attn_fwd_scratch_limit_bytes(Dt dt, const AttnShape& a) {
+  return attn_fwd_partial_bytes(a, grid_split_plan(dt, a));
+}
+
 AttnSplit attn_bwd_split_plan(Dt dt, const AttnShape& a) {
-  AttnSplit p = attn_split_plan(dt, a);
+  const AttnSplit whole{kUnsplit, 1, kUnsplit, 1}, p = grid_split_plan(dt, a);
   // both roles share one launch: split only when together they are too few
   const long long blocks = (long long)((a.seq + kBlockK - 1) / kBlockK +
                                        (a.seq + kBlockQ - 1) / kBlockQ) * a.heads * a.batch;
-  if (blocks * kWavesK >= kSplitBelow) p = AttnSplit{kUnsplit, 1, kUnsplit, 1};
-  return p;
+  if (blocks * kWavesK >= kSplitBelow) return whole;
+  auto longest_us = [&](int kv, int q) { return std::max(1.05 * kv, 2.1 * q); };
+  const double merge_us = 8.0 + 2.0 * attn_bwd_partial_bytes(a, p) / 1e7;
+  const double saved_us =
+      longest_us(p.kv_tiles, p.fwd_tiles) -
+      longest_us(std::min(p.kv_tiles, p.kv_chunk), std::min(p.fwd_tiles, p.fwd_chunk));
+  return saved_us < merge_us ? whole : p;
 }
 
 size_t attn_fwd_partial_bytes(const AttnShape& a, const AttnSplit& p) {

@@ -232,11 +232,16 @@ struct AttnShape {
 struct AttnSplit {
   int fwd_chunk, fwd_n;  // forward and dQ: key tiles of 64
   int kv_chunk, kv_n;    // dK/dV: query tiles of 32
+  int fwd_tiles = 0, kv_tiles = 0;  // tiles of the longest block (0: not counted)
 };
 AttnSplit attn_split_plan(Dt dt, const AttnShape& a);
 // The backward's plan: both backward roles run in one launch, so it splits
 // only when their blocks together are too few for the chip.
 AttnSplit attn_bwd_split_plan(Dt dt, const AttnShape& a);
+// What the allocation-free entry point measures against its fixed scratch: the
+// partial results of a forward split as finely as its grid alone asks for (at
+// least those of attn_split_plan, which keeps short blocks whole).
+size_t attn_fwd_scratch_limit_bytes(Dt dt, const AttnShape& a);
 // Bytes of partial results the split forward / backward needs (0: unsplit).
 size_t attn_fwd_partial_bytes(const AttnShape& a, const AttnSplit& p);
 size_t attn_bwd_partial_bytes(const AttnShape& a, const AttnSplit& p);

@@ -832,12 +832,13 @@ pb_status pblock_swattn_forward_noalloc(const pb_config* cfg, const void* q, con
   a.heads = cfg->heads;
   a.head_dim = cfg->head_dim;
   a.window = cfg->window < cfg->seq ? cfg->window : cfg->seq;
-  const size_t need = pb::attn_fwd_partial_bytes(a, pb::attn_split_plan(dt_of(cfg), a));
-  if (need > kNoallocScratchBytes)
+  const size_t limit = pb::attn_fwd_scratch_limit_bytes(dt_of(cfg), a);
+  if (limit > kNoallocScratchBytes)
     return fail(PB_ERR_UNSUPPORTED,
                 "this shape's split forward needs %zu bytes of scratch, more than the %zu the "
                 "allocation-free entry point holds; use pblock_swattn_forward with a workspace",
-                need, kNoallocScratchBytes);
+                limit, kNoallocScratchBytes);
+  const size_t need = pb::attn_fwd_partial_bytes(a, pb::attn_split_plan(dt_of(cfg), a));
   void* ws = nullptr;
   if (need) PB_CHECK(scratch_address(&ws));
   pb::launch_attn_forward(dt_of(cfg), a, q, k, v, ld_qkv, o, ld_o, lse, ws, need, stream);
