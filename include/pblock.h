@@ -238,6 +238,7 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x,
  * output tiles; when the last wave of tiles is partial (or the whole grid is
  * smaller than the 256 compute units), each of its `tail` tiles is split
  * into `splits` K-slices whose fp32 partial tiles a second kernel sums.
+ * Small bf16 grids take whole 64 x 64 tiles instead (tiles counts those).
  * Fills tiles, n_full (tiles computed whole), tail, splits (1: no split),
  * workgroups (of the GEMM kernel: n_full + tail * splits) and threads (per
  * workgroup).  fp32 GEMMs have tiles of 64 x 64, all of them split along K

@@ -1093,6 +1093,36 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float* __restrict__ p
   }
 }
 
+// Launch times of the 256 x 256 tiles and of the 64 x 64 tiles of
+// gemm_small.hip, in us, fitted to both measured on shapes from 128 x 256 x 512
+// to 2048 x 2048 x 512 (mostly within 10%):
+//  - 256 x 256: 0.95 us a K-tile with part of the chip busy, 9.5 us around it
+//    (launch, prologue, epilogue, code fetched cold); a split adds its sum's
+//    launch and the partial tiles;
+//  - 64 x 64: a CU takes a tile at a time, 4.6 us per 1024 k where B is
+//    MN-contiguous, 6.8 where both operands are K-contiguous (half lines); one
+//    figure for both, so that a plan depends on the sizes alone.
+// E.g. (256, 64): 128 x 256 x 512 12 and 6.5 us, 256 x 2560 x 512 16.5 and 7,
+// 512 x 2048 x 2048 23 and 14 to 18, 1024 x 2048 x 2048 26 and 25 to 33.
+constexpr double kStepUs = 0.95, kTileUs = 9.5;
+double split_sum_us(int parts) { return 4.5 + 0.03 * parts; }
+// (a CU's first tile, or one of several: their sums and epilogues then queue)
+double small_tile_us(int K, bool several) { return (several ? 2.0 : 0.5) + 5.7 * K / 1024; }
+bool gemm_small_wins(int M, int N, int K) {
+  const SplitPlan p = gemm_split_plan(Dt::BF16, M, N, K);
+  const int nk = (K + kBK - 1) / kBK;
+  // (a single 256 x 256 tile, of at most four K-tiles, keeps its plan)
+  if (p.n_full == 1 && p.tail == 0) return false;
+  double big = kTileUs + kStepUs * ((p.n_full + kCUs - 1) / kCUs) * nk;
+  if (p.tail) {
+    const int waves = (p.tail * p.splits + kCUs - 1) / kCUs;
+    big += kStepUs * waves * ((nk + p.splits - 1) / p.splits);
+    if (p.splits > 1) big += split_sum_us(p.tail * p.splits);
+  }
+  const int tiles = gemm_small_tiles(M, N);
+  return 4.0 + (tiles + kCUs - 1) / kCUs * small_tile_us(K, tiles > kCUs) < 0.95 * big;
+}
+
 // The DMA path addresses a tile as scalar base + 32-bit lane offset.
 bool dma_offsets_fit(bool ak, int lda, bool bk, int ldb) {
   auto fits = [](bool kc, int ld) {
@@ -1104,6 +1134,10 @@ bool dma_offsets_fit(bool ak, int lda, bool bk, int ldb) {
 template <bool AK, bool BK, Epi EPI, bool GT>
 void gemm_dispatch(Dt dt, const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                    const EpiArgs& ep, float* split_ws, size_t split_ws_floats, hipStream_t s) {
+  if (gemm_small_wins(M, N, K)) {
+    launch_gemm_small(GemmSpec{EPI, AK, BK, A, lda, B, ldb, M, N, K, ep}, s);
+    return;
+  }
   const int tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
   const size_t lds = 4 * (size_t)kTileBytes;  // both kernels: 128 KB
   static_assert(kStages * 2 * kDTile == 4 * kTileBytes, "DMA path LDS");
@@ -1158,6 +1192,7 @@ SplitPlan gemm_split_plan(Dt dt, int M, int N, int K) {
 }
 
 size_t gemm_split_floats(Dt dt, int M, int N, int K) {
+  if (dt == Dt::BF16 && gemm_small_wins(M, N, K)) return 0;
   const SplitPlan p = dt == Dt::F32 ? gemm_f32_launch_of(M, N, K).plan
                                     : gemm_split_plan(dt, M, N, K);
   return (size_t)p.tail * p.splits * kBM * kBN;
@@ -1165,7 +1200,12 @@ size_t gemm_split_floats(Dt dt, int M, int N, int K) {
 
 GemmLaunch gemm_launch_of(Dt dt, int M, int N, int K) {
   GemmLaunch g;
-  if (dt == Dt::BF16) {
+  if (dt == Dt::BF16 && gemm_small_wins(M, N, K)) {
+    g.tiles = gemm_small_tiles(M, N);
+    g.plan = SplitPlan{g.tiles, 0, 1};
+    g.workgroups = g.tiles;
+    g.threads = gemm_small_threads();
+  } else if (dt == Dt::BF16) {
     g.tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
     g.plan = gemm_split_plan(dt, M, N, K);
     g.workgroups = g.plan.n_full + g.plan.tail * g.plan.splits;
@@ -1177,9 +1217,9 @@ GemmLaunch gemm_launch_of(Dt dt, int M, int N, int K) {
 }
 
 bool gemm_rowsum_supported(Dt dt, const GemmSpec& g, size_t ws_floats) {
-  if (dt != Dt::BF16 || g.epi != Epi::StoreF32 ||
-      !dma_offsets_fit(g.a_kcontig, g.lda, g.b_kcontig, g.ldb))
-    return false;
+  if (dt != Dt::BF16 || g.epi != Epi::StoreF32) return false;
+  if (gemm_small_wins(g.M, g.N, g.K)) return true;
+  if (!dma_offsets_fit(g.a_kcontig, g.lda, g.b_kcontig, g.ldb)) return false;
   const size_t split = gemm_split_floats(dt, g.M, g.N, g.K);
   return split == 0 || ws_floats < split;  // launched unsplit
 }
@@ -1213,7 +1253,7 @@ void launch_queue_reset(int* queue, int n, hipStream_t s) {
 // of 2048 tokens, hidden 12288, 16 heads of 96 (dO + dW_o: 48 tiles of 192
 // K-tiles beside 288 of 32) 2675 -> 2609 us for the whole step.  2048 tokens
 // at hidden 4096 and above stay whole.
-int gemm_pair_splits(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats) {
+static int pair_splits(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats, double* steps) {
   const int t1 = tiles_of(g1), t2 = tiles_of(g2), nk1 = g1.K / kBK, nk2 = g2.K / kBK;
   auto cost = [&](int s) {
     const int n1 = t1 * s, a = (nk1 + s - 1) / s;
@@ -1226,11 +1266,31 @@ int gemm_pair_splits(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats) {
   int best = 1;
   for (int s = 2; s <= std::min(16, nk1); ++s)
     if ((size_t)t1 * s * kBM * kBN <= ws_floats && cost(s) < cost(best)) best = s;
+  if (steps) *steps = cost(best) - (best > 1 ? 4.0 + t1 * best / 16.0 : 0);
   return best;
+}
+int gemm_pair_splits(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats) {
+  return pair_splits(g1, g2, ws_floats, nullptr);
+}
+
+// The shared launch in 64 x 64 tiles: against its end in 256 x 256 ones, as
+// gemm_small_wins.
+static bool pair_small_wins(const GemmSpec& g1, const GemmSpec& g2) {
+  double steps = 0;
+  const int splits = pair_splits(g1, g2, SIZE_MAX, &steps);
+  const double big = kTileUs + kStepUs * steps + (splits > 1 ? split_sum_us(tiles_of(g1) * splits) : 0);
+  const double u1 = small_tile_us(g1.K, true), u2 = small_tile_us(g2.K, true);
+  const int t1 = gemm_small_tiles(g1.M, g1.N), t2 = gemm_small_tiles(g2.M, g2.N);
+  const double all = (t1 * u1 + t2 * u2) / kCUs + (t1 + t2 > kCUs ? 0.5 * std::min(u1, u2) : 0);
+  return 4.0 + std::max(all, std::max(u1, u2)) < 0.95 * big;
+}
+
+bool gemm_pair_whole(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats) {
+  return !pair_small_wins(g1, g2) && gemm_pair_splits(g1, g2, ws_floats) == 1;
 }
 
 size_t gemm_pair_split_floats(Dt dt, const GemmSpec& g1, const GemmSpec& g2) {
-  if (!gemm_pair_supported(dt, g1, g2)) return 0;
+  if (!gemm_pair_supported(dt, g1, g2) || pair_small_wins(g1, g2)) return 0;
   const int s = gemm_pair_splits(g1, g2, SIZE_MAX);
   return s > 1 ? (size_t)tiles_of(g1) * s * kBM * kBN : 0;
 }
@@ -1244,6 +1304,10 @@ bool launch_gemm_pair(Dt dt, const GemmSpec& g1, const GemmSpec& g2, int* queue,
   const DmaGemm d1 = desc(g1), d2 = desc(g2);
   const int t1 = tiles_of(g1), t2 = tiles_of(g2);
   const size_t lds = 4 * (size_t)kTileBytes;
+  if (pair_small_wins(g1, g2)) {
+    launch_gemm_small_pair(g1, g2, s);
+    return true;
+  }
   const int splits = split_ws ? gemm_pair_splits(g1, g2, split_ws_floats) : 1;
   if (splits > 1) {
     gemm_bf16_dma_pair_split<true, false, false, false>

@@ -207,10 +207,18 @@ bool gemm_pair_supported(Dt dt, const GemmSpec& g1, const GemmSpec& g2);
 // Whether launch_gemm of a weight gradient, given ws_floats of split space,
 // forms rowsum.
 bool gemm_rowsum_supported(Dt dt, const GemmSpec& g, size_t ws_floats);
+// The kernels of small grids (gemm_small.hip: 64 x 64 tiles, no split space).
+int gemm_small_tiles(int M, int N);
+int gemm_small_threads();
+void launch_gemm_small(const GemmSpec& g, hipStream_t s);
+void launch_gemm_small_pair(const GemmSpec& g1, const GemmSpec& g2, hipStream_t s);
 // K-slices per tile of the first GEMM in the shared launch of a supported pair,
-// given ws_floats of space for partial tiles (1: whole tiles, and the first
-// GEMM's epilogue forms delta when asked to; a split launch does not).
+// given ws_floats of space for partial tiles (1: whole tiles).
 int gemm_pair_splits(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats);
+// Whether a supported pair's launch computes whole 256 x 256 tiles (neither
+// split nor a small grid's): it then takes a queue, and the first GEMM's
+// epilogue forms delta when asked to.
+bool gemm_pair_whole(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats);
 size_t gemm_pair_split_floats(Dt dt, const GemmSpec& g1, const GemmSpec& g2);
 bool launch_gemm_pair(Dt dt, const GemmSpec& g1, const GemmSpec& g2, int* queue, float* split_ws,
                       size_t split_ws_floats, hipStream_t s);

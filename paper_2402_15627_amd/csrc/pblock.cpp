@@ -675,12 +675,12 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x, const void*
   // leaves the accumulators, instead of re-reading dO and O in a launch of
   // their own: heads of 64 or 128 columns whose blocks align with the
   // epilogue's 128-column wave blocks.
-  const bool whole_out = pair_out && pb::gemm_pair_splits(g_dc, g_dwo, split_f) == 1;
+  const bool whole_out = pair_out && pb::gemm_pair_whole(g_dc, g_dwo, split_f);
   const bool delta_in_dc = whole_out && (d.d == 64 || d.d == 128) && A % 128 == 0;
   // db_in = sum over tokens of dZ: the row sums of dW_in's A operand (dZ^T),
   // formed by the first tile column of dW_in, in the shared launch or alone
   const bool pair_in = pb::gemm_pair_supported(dt, g_dh, g_dwi);
-  const bool whole_in = pair_in && pb::gemm_pair_splits(g_dh, g_dwi, split_f) == 1;
+  const bool whole_in = pair_in && pb::gemm_pair_whole(g_dh, g_dwi, split_f);
   const bool db_in_fused = pair_in || pb::gemm_rowsum_supported(dt, g_dwi, split_f);
   if (db_in_fused) G.dw_in.ep.rowsum = db_in;
   if (delta_in_dc) {
@@ -1155,7 +1155,7 @@ pb_status pblock_serial_backward(const pb_config* cfg, const void* x, const void
     G.dw_qkv.ep.rowsum = db_in;
   }
   const bool delta_in_do = pb::gemm_pair_supported(dt, G.d_o, G.dw_o) &&
-                           pb::gemm_pair_splits(G.d_o, G.dw_o, split_f) == 1 &&
+                           pb::gemm_pair_whole(G.d_o, G.dw_o, split_f) &&
                            (d.d == 64 || d.d == 128) && A % 128 == 0;
   if (delta_in_do) {
     G.d_o.ep.o_rows = c;  // O = C[:, :A]
@@ -1175,7 +1175,7 @@ pb_status pblock_serial_backward(const pb_config* cfg, const void* x, const void
   // heads, zeroed here
   static_assert(kBwdQueueSets >= 4, "one queue per shared launch");
   auto whole_pair = [&](const pb::GemmSpec& g, const pb::GemmSpec& wg) {
-    return pb::gemm_pair_supported(dt, g, wg) && pb::gemm_pair_splits(g, wg, split_f) == 1;
+    return pb::gemm_pair_supported(dt, g, wg) && pb::gemm_pair_whole(g, wg, split_f);
   };
   if (whole_pair(G.dg, G.dw_down) || whole_pair(G.dh2, G.dw_up) || whole_pair(G.d_o, G.dw_o) ||
       whole_pair(G.dh1, G.dw_qkv))

@@ -10,11 +10,11 @@ from tests.parity_util import GRAD_NAMES, TOL, compare, case, normwise, run_orac
 pytestmark = pytest.mark.gpu
 
 SHAPES = [
-    # dh: one tile of 2560 / 64 = 40 K-tiles; dC: six tiles of 8
-    BlockShape("pair_split_dh", 1, 256, 512, 4, 128, 1024, 96, "bf16"),
-    # both split, ragged tile edges, K-tiles that do not divide evenly
-    BlockShape("pair_split_both", 2, 96, 1088, 4, 64, 1984, 50, "bf16"),
-    BlockShape("pair_split_erf", 1, 128, 1024, 4, 128, 4096, 128, "bf16", gelu_tanh=False),
+    # dh: four tiles of 9728 / 64 = 152 K-tiles
+    BlockShape("pair_split_dh", 1, 128, 1024, 4, 128, 8192, 96, "bf16"),
+    # ragged tile edges, several batch rows, heads of 64
+    BlockShape("pair_split_d64", 3, 128, 2112, 8, 64, 4160, 50, "bf16"),
+    BlockShape("pair_split_erf", 1, 384, 2048, 8, 128, 4096, 128, "bf16", gelu_tanh=False),
 ]
 
 

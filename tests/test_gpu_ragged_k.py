@@ -1,5 +1,5 @@
 """bf16 GEMMs whose contraction length is no multiple of 64: the last K-tile is
-loaded clamped and zeroed in LDS past the end.  Blocks against the oracle with
+loaded clamped and zeroed past the end.  Blocks against the oracle with
 ragged token counts (the weight gradients contract over them), hidden and FFN
 widths (every other GEMM does), last K-tiles of 1 to 63 rows or 8 to 56
 columns, whole and K-split launches."""
@@ -15,14 +15,14 @@ SHAPES = [
     BlockShape("k_short", 1, 3, 72, 1, 64, 8, 2, "bf16"),      # K below one tile
     # dW_in 9216 x 2048 over 300 tokens: 288 tiles, 256 of them whole
     BlockShape("k_whole", 1, 300, 2048, 16, 128, 3072, 150, "bf16"),
-    # in-projection 2 x 12 tiles split along K = 1096 (18 K-tiles, the last of 8)
-    BlockShape("k_split", 1, 300, 1096, 4, 128, 1288, 100, "bf16", gelu_tanh=False),
+    # dh 2 x 5 tiles split along K = 4872 (77 K-tiles, the last of 8)
+    BlockShape("k_split", 1, 300, 1096, 4, 128, 3336, 100, "bf16", gelu_tanh=False),
 ]
 
 
 def test_ragged_plans():
-    p = pb.pblock_gemm_plan(pb.PB_BF16, 300, 2824, 1096)
-    assert (p.tiles, p.n_full, p.tail) == (24, 0, 24) and p.splits > 1
+    p = pb.pblock_gemm_plan(pb.PB_BF16, 300, 1096, 4872)
+    assert (p.tiles, p.n_full, p.tail) == (10, 0, 10) and p.splits > 1
     p = pb.pblock_gemm_plan(pb.PB_BF16, 9216, 2048, 300)
     assert (p.tiles, p.n_full, p.tail, p.splits) == (288, 256, 32, 5)
     assert pb.pblock_backward_pairs(pb.config_from_shape(SHAPES[0])) == (False, False)
