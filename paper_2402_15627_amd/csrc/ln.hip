@@ -7,6 +7,8 @@
 // write of h, statistics from wavefront reductions.  Backward: the two row
 // reductions it needs are formed by the dh GEMM's epilogue (Epi::LnGrad), so
 // the kernel here is column-parallel and streams x, dh and dy once.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -206,7 +208,12 @@ constexpr int kApplyRows = 16;
 constexpr int kApplyThreads = 256;
 constexpr int kApplyCols = kApplyThreads * 8;
 
-template <typename T>
+// RG > 1, for rows of at most 2048 / RG columns: RG groups of threads take every
+// RG-th row of the 16 and their column sums are added through LDS in group
+// order.  One group would leave most threads idle and walk the 16 rows in
+// series, which is all of such a launch's time (256 rows of 512 columns 8.7 -> 5.2 us,
+// 128 rows of 256 in fp32 9.3 -> 5.7).
+template <typename T, int RG>
 __global__ __launch_bounds__(kApplyThreads) void ln_bwd_apply(
     const T* __restrict__ x, const float* __restrict__ mean, const float* __restrict__ rstd,
     const T* __restrict__ gamma, const T* __restrict__ dh, const float2* __restrict__ rowpart,
@@ -217,7 +224,9 @@ __global__ __launch_bounds__(kApplyThreads) void ln_bwd_apply(
   const int cb = (int)blockIdx.x % ncb, chunk = (int)blockIdx.x / ncb;
   const int r0 = chunk * kApplyRows;
   const int nr = min(kApplyRows, rows - r0);
-  const int c = (cb * kApplyThreads + threadIdx.x) * 8;
+  constexpr int kGroup = kApplyThreads / RG;  // threads per row
+  const int rg = threadIdx.x / kGroup;
+  const int c = (cb * kApplyThreads + (int)threadIdx.x % kGroup) * 8;
   const bool col_ok = c < H;
   float gm[8], adg[8], adb[8], ady[8];
   // the first rows' loads go out before the row terms are folded (they do
@@ -231,12 +240,14 @@ __global__ __launch_bounds__(kApplyThreads) void ln_bwd_apply(
   // after the previous stores, every batch paid the full load latency).
   // bf16 rows are held packed, four to a batch (four batches per workgroup
   // instead of eight, with the same registers).
-  constexpr int kBatch = sizeof(T) == 2 ? 4 : 2, kBatches = kApplyRows / kBatch;
+  constexpr int kMyRows = kApplyRows / RG;  // rows rg, rg + RG, ...
+  constexpr int kBatch = kMyRows < 4 ? kMyRows : sizeof(T) == 2 ? 4 : 2;
+  constexpr int kBatches = kMyRows / kBatch;
   Raw8<T> xv[2][kBatch], dv[2][kBatch], yv[2][kBatch];
   auto load_batch = [&](int buf, int rb) {
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
-      const size_t off = (size_t)(r0 + min(rb + i, nr - 1)) * H + c;
+      const size_t off = (size_t)(r0 + min((rb + i) * RG + rg, nr - 1)) * H + c;
       xv[buf][i].load(x + off);
       dv[buf][i].load(dh + off);
       yv[buf][i].load(dy + off);
@@ -266,16 +277,17 @@ __global__ __launch_bounds__(kApplyThreads) void ln_bwd_apply(
     }
   }
   __syncthreads();
-  if (!col_ok) return;
+  if (RG == 1 && !col_ok) return;
 
 #pragma unroll
   for (int bt = 0; bt < kBatches; ++bt) {
     const int cur = bt & 1;
-    if (bt + 1 < kBatches && (bt + 1) * kBatch < nr) load_batch(cur ^ 1, (bt + 1) * kBatch);
+    if (bt + 1 < kBatches && (bt + 1) * kBatch * RG < nr && col_ok)
+      load_batch(cur ^ 1, (bt + 1) * kBatch);
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
-      const int rr = bt * kBatch + i;
-      if (rr < nr) {
+      const int rr = (bt * kBatch + i) * RG + rg;
+      if (rr < nr && col_ok) {
         const size_t off = (size_t)(r0 + rr) * H + c;
         const float m1 = stat[rr][0], m2 = stat[rr][1], mu = stat[rr][2], rs = stat[rr][3];
         float o[8];
@@ -299,6 +311,23 @@ __global__ __launch_bounds__(kApplyThreads) void ln_bwd_apply(
             store8(dx + off, o);
         }
       }
+    }
+  }
+  if constexpr (RG > 1) {
+    __shared__ float sums[RG - 1][kGroup][25];  // 24 values, padded
+    if (rg > 0) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float* p = sums[rg - 1][threadIdx.x % kGroup];
+        p[e] = adg[e], p[8 + e] = adb[e], p[16 + e] = ady[e];
+      }
+    }
+    __syncthreads();
+    if (rg > 0 || !col_ok) return;
+    for (int w = 0; w < RG - 1; ++w) {
+      const float* p = sums[w][threadIdx.x];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) adg[e] += p[e], adb[e] += p[8 + e], ady[e] += p[16 + e];
     }
   }
   const size_t prow = (size_t)chunk * H + c;
@@ -459,16 +488,20 @@ void launch_ln_backward(Dt dt, const void* x, const float* mean, const float* rs
                         float* part_dy, int rows, int H, hipStream_t s) {
   const unsigned grid = (unsigned)((H + kApplyCols - 1) / kApplyCols) * ln_backward_chunks(rows);
   const int ng = ln_row_groups(H);
-  if (dt == Dt::BF16)
-    ln_bwd_apply<bf16><<<grid, kApplyThreads, 0, s>>>(
-        (const bf16*)x, mean, rstd, (const bf16*)gamma, (const bf16*)dh, rowpart, ng,
-        (const bf16*)dy,
-        (bf16*)dx, part_dgamma, part_dbeta, part_dy, rows, H);
-  else
-    ln_bwd_apply<float><<<grid, kApplyThreads, 0, s>>>(
-        (const float*)x, mean, rstd, (const float*)gamma, (const float*)dh, rowpart, ng,
-        (const float*)dy,
-        (float*)dx, part_dgamma, part_dbeta, part_dy, rows, H);
+  auto run = [&](auto t, auto rg) {
+    typedef decltype(t) T;
+    ln_bwd_apply<T, decltype(rg)::value><<<grid, kApplyThreads, 0, s>>>(
+        (const T*)x, mean, rstd, (const T*)gamma, (const T*)dh, rowpart, ng, (const T*)dy, (T*)dx,
+        part_dgamma, part_dbeta, part_dy, rows, H);
+  };
+  auto pick = [&](auto t) {
+    if (H <= kApplyCols / 8) run(t, std::integral_constant<int, 8>{});
+    else if (H <= kApplyCols / 4) run(t, std::integral_constant<int, 4>{});
+    else if (H <= kApplyCols / 2) run(t, std::integral_constant<int, 2>{});
+    else run(t, std::integral_constant<int, 1>{});
+  };
+  if (dt == Dt::BF16) pick(bf16{});
+  else pick(float{});
 }
 
 size_t colsum_partial_floats(int rows, int cols) {
