@@ -1217,7 +1217,8 @@ GemmLaunch gemm_launch_of(Dt dt, int M, int N, int K) {
 }
 
 bool gemm_rowsum_supported(Dt dt, const GemmSpec& g, size_t ws_floats) {
-  if (dt != Dt::BF16 || g.epi != Epi::StoreF32) return false;
+  if (g.epi != Epi::StoreF32) return false;
+  if (dt == Dt::F32) return gemm_f32_rowsum_supported(g.M, g.N, g.K, ws_floats);
   if (gemm_small_wins(g.M, g.N, g.K)) return true;
   if (!dma_offsets_fit(g.a_kcontig, g.lda, g.b_kcontig, g.ldb)) return false;
   const size_t split = gemm_split_floats(dt, g.M, g.N, g.K);

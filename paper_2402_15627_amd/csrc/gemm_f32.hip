@@ -129,6 +129,10 @@ __global__ __launch_bounds__(kFThreads) void gemm_f32_kernel(const float* __rest
   f32x4 acc[4];
 #pragma unroll
   for (int n = 0; n < 4; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // the row sums of A, when asked for, from the first tile column: this lane's
+  // share of row wm + fr
+  const bool rows = EPI == Epi::StoreF32 && ep.rowsum && tn == 0;
+  float rsum = 0.f;
   TA ta;
   TB tb;
   ta.init(A, lda, m0, M);
@@ -161,6 +165,8 @@ __global__ __launch_bounds__(kFThreads) void gemm_f32_kernel(const float* __rest
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       a[ks] = TA::frag(la, wm + fr, ks, g);
+      if constexpr (EPI == Epi::StoreF32)
+        if (rows) rsum += (a[ks][0] + a[ks][1]) + (a[ks][2] + a[ks][3]);
 #pragma unroll
       for (int n = 0; n < 4; ++n) b[ks][n] = TB::frag(lb, 16 * n + fr, ks, g);
     }
@@ -195,6 +201,11 @@ __global__ __launch_bounds__(kFThreads) void gemm_f32_kernel(const float* __rest
       if (mok && c < N) *reinterpret_cast<f32x4*>(row + c) = acc[n];
     }
     return;
+  }
+  if (rows) {
+    rsum += __shfl_xor(rsum, 16, 64);
+    rsum += __shfl_xor(rsum, 32, 64);
+    if (g == 0 && mok) ep.rowsum[m] = rsum;
   }
   float s1 = 0.f, s2 = 0.f, mu = 0.f, rs = 0.f;
   if (EPI == Epi::LnGrad && mok) mu = ep.mean[m], rs = ep.rstd[m];
@@ -289,6 +300,7 @@ __global__ __launch_bounds__(kSThreads) void gemm_f32_waves_kernel(
     const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb, int M, int N,
     int K, EpiArgs ep) {
   __shared__ __attribute__((aligned(16))) float smem[kSW * 16 * kFN];
+  __shared__ float rbuf[EPI == Epi::StoreF32 ? kSW * 16 : 1];
   const int tiles_m = (M + 15) / 16, tiles_n = (N + kFN - 1) / kFN;
   int tm, tn;
   tile_of<32>(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
@@ -299,6 +311,8 @@ __global__ __launch_bounds__(kSThreads) void gemm_f32_waves_kernel(
   f32x4 acc[4];
 #pragma unroll
   for (int n = 0; n < 4; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool rows = EPI == Epi::StoreF32 && ep.rowsum && tn == 0;
+  float rsum = 0.f;
   F32Frags<AK, 1> fa;
   F32Frags<BK, 4> fb;
   fa.init(A, lda, m0, M, wave, fr, g);
@@ -311,6 +325,13 @@ __global__ __launch_bounds__(kSThreads) void gemm_f32_waves_kernel(
   };
   auto mma = [&](auto S) {
     constexpr int s = decltype(S)::value;
+    if constexpr (EPI == Epi::StoreF32) {
+      if (rows) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+          rsum += (a[s][ks][0][0] + a[s][ks][0][1]) + (a[s][ks][0][2] + a[s][ks][0][3]);
+      }
+    }
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -336,8 +357,22 @@ __global__ __launch_bounds__(kSThreads) void gemm_f32_waves_kernel(
 #pragma unroll
   for (int n = 0; n < 4; ++n)
     *reinterpret_cast<f32x4*>(smem + (wave * 16 + fr) * kFN + 16 * n + 4 * g) = acc[n];
+  if constexpr (EPI == Epi::StoreF32) {
+    if (rows) {
+      rsum += __shfl_xor(rsum, 16, 64);
+      rsum += __shfl_xor(rsum, 32, 64);
+      if (g == 0) rbuf[wave * 16 + fr] = rsum;
+    }
+  }
   __syncthreads();
   if (threadIdx.x >= 256) return;
+  if constexpr (EPI == Epi::StoreF32) {
+    if (rows && threadIdx.x < 16 && m0 + (int)threadIdx.x < M) {
+      float v = 0.f;
+      for (int w = 0; w < kSW; ++w) v += rbuf[w * 16 + threadIdx.x];
+      ep.rowsum[m0 + threadIdx.x] = v;
+    }
+  }
   const int row = threadIdx.x >> 4, c4 = 4 * (threadIdx.x & 15);
   f32x4 sum = *reinterpret_cast<const f32x4*>(smem + row * kFN + c4);
 #pragma unroll
@@ -449,11 +484,17 @@ GemmLaunch launch_of(const F32Plan& p, int M, int N) {
   return g;
 }
 
+// The plan of a launch that has ws_floats of space for slices.
+F32Plan launched_plan(int M, int N, int K, size_t ws_floats) {
+  const F32Plan p = f32_plan(M, N, K, true);
+  return p.splits > 1 && ws_floats < gemm_split_floats(Dt::F32, M, N, K) ? f32_plan(M, N, K, false)
+                                                                         : p;
+}
+
 template <bool AK, bool BK, Epi EPI, bool GT>
 void launch_layout(const float* A, int lda, const float* B, int ldb, int M, int N, int K,
                    const EpiArgs& ep, float* ws, size_t ws_floats, hipStream_t s) {
-  F32Plan p = f32_plan(M, N, K, true);
-  if (p.splits > 1 && (!ws || ws_floats < gemm_split_floats(Dt::F32, M, N, K))) p = f32_plan(M, N, K, false);
+  const F32Plan p = launched_plan(M, N, K, ws ? ws_floats : 0);
   const GemmLaunch g = launch_of(p, M, N);
   if (p.rows == 16) {
     gemm_f32_waves_kernel<AK, BK, EPI, GT>
@@ -470,6 +511,10 @@ void launch_layout(const float* A, int lda, const float* B, int ldb, int M, int 
 }
 
 }  // namespace
+
+bool gemm_f32_rowsum_supported(int M, int N, int K, size_t ws_floats) {
+  return launched_plan(M, N, K, ws_floats).splits == 1;
+}
 
 GemmLaunch gemm_f32_launch_of(int M, int N, int K) {
   return launch_of(f32_plan(M, N, K, true), M, N);

@@ -165,6 +165,7 @@ GemmLaunch gemm_launch_of(Dt dt, int M, int N, int K);
 // The fp32 GEMMs (gemm_f32.hip): tiles of 64 x 64 (whole, or every tile split
 // along K, its slices' partial results summed by a second kernel) or 16 x 64.
 GemmLaunch gemm_f32_launch_of(int M, int N, int K);
+bool gemm_f32_rowsum_supported(int M, int N, int K, size_t ws_floats);
 void launch_gemm_f32(Epi epi, bool a_kcontig, bool b_kcontig, const float* A, int lda,
                      const float* B, int ldb, int M, int N, int K, const EpiArgs& ep, float* ws,
                      size_t ws_floats, hipStream_t s);
