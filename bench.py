@@ -197,6 +197,10 @@ def gemm_step_of(name, grid, s, block="parallel"):
                             if "persistent" in name else tiles(a) + tiles(b))
         hits = [f"{a}+{b}" for a, b in paired_steps(s, block).items()
                 if GEMM_SIGNATURE[a] in name and wgs(a, b) * 512 == grid]
+        if "pair_split" in name:  # the first GEMM's tiles in two or more K-slices each
+            slices = lambda a, b: divmod(grid // 512 - tiles(b), tiles(a))  # noqa: E731
+            hits = [f"{a}+{b}" for a, b in paired_steps(s, block).items()
+                    if slices(a, b)[0] > 1 and slices(a, b)[1] == 0]
         return "/".join(hits)
     hits = [st for st, mnk in steps.items()
             if "gemm_bf16" in name and GEMM_SIGNATURE[st] in name

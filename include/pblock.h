@@ -124,8 +124,9 @@ pb_status pblock_saved_offsets(const pb_config* cfg, size_t* offsets);
  *   PB_WS_FORWARD_WITH_STASH  pblock_forward with saved == NULL: the stash is
  *                             kept at the start of ws
  *   PB_WS_BACKWARD            pblock_backward
- * The sizes include a region for tail-split GEMM partial tiles (the last,
- * partial wave of output tiles is split along K so the chip stays full).
+ * The sizes include a region for the partial tiles of GEMMs split along K
+ * (the last, partial wave of output tiles, or all tiles of a small grid, so
+ * the chip stays full; fp32 and bf16, also inside shared launches).
  * That region is optional: a smaller ws (down to 0 bytes for PB_WS_FORWARD,
  * the stash for PB_WS_FORWARD_WITH_STASH, and the size without the region
  * for PB_WS_BACKWARD) also works, unsplit (results then differ only in
@@ -147,7 +148,7 @@ typedef enum {
   PB_STEP_DH,         /* dh = dZ W_in                                       */
   PB_STEP_DW_IN,      /* dW_in = dZ^T h                                     */
   PB_STEP_DB_IN,      /* db_in = sum over tokens of dZ; empty when formed
-                         in dW_in's launch shared with dh                 */
+                         in dW_in's launch, shared with dh or its own     */
   PB_STEP_LN_BWD,     /* dx = dy + LN backward; dgamma, dbeta, db_out       */
   PB_STEP_COUNT
 } pb_step;
@@ -157,9 +158,9 @@ typedef enum {
  * launches of step i and end[i] just after them; NULL entries, and a NULL
  * pb_step_events, are skipped.  The events belong to the caller and are
  * only recorded, never waited on.  A step whose work shares a launch with
- * another step records nothing between its events (PB_STEP_DW_OUT, and
- * PB_STEP_DW_IN and PB_STEP_DB_IN, when pblock_backward_pairs reports the
- * pair; PB_STEP_DB_OUT always). */
+ * another step records nothing between its events (PB_STEP_DW_OUT and
+ * PB_STEP_DW_IN when pblock_backward_pairs reports the pair; PB_STEP_DB_IN
+ * where dW_in's launch forms it; PB_STEP_DB_OUT always). */
 typedef struct {
   hipEvent_t begin[PB_STEP_COUNT];
   hipEvent_t end[PB_STEP_COUNT];
@@ -204,11 +205,11 @@ pb_status pblock_workspace_offsets(const pb_config* cfg, size_t* offsets);
  * activation dtype; the six parameter gradients are fp32 and overwritten.
  * ws should hold pblock_workspace_bytes(cfg, PB_WS_BACKWARD) bytes (fewer,
  * down to the size without the GEMM partial-tile region, also works).
- * Where dC and dW_out (dh and dW_in) share a launch, that launch is
- * persistent: one workgroup per CU takes tiles from per-XCD queues whose
- * heads live in ws and are zeroed by the call itself, so ws needs no
- * initialisation and two calls in flight at once need separate workspaces
- * (as for every other region of ws). */
+ * Where dC and dW_out (dh and dW_in) share a launch of whole 256 x 256 tiles,
+ * that launch is persistent: one workgroup per CU takes tiles from per-XCD
+ * queues whose heads live in ws and are zeroed by the call itself, so ws
+ * needs no initialisation and two calls in flight at once need separate
+ * workspaces (as for every other region of ws). */
 pb_status pblock_backward(const pb_config* cfg, const void* x,
                           const void* ln_gamma, const void* ln_beta,
                           const void* w_in, const void* b_in,
@@ -250,8 +251,10 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x,
  * weight-gradient GEMM after them (1) or launch alone (0).  block 0, the
  * parallel block: paired[0] = dC with dW_out, paired[1] = dh with dW_in.
  * block 1, the serial block: paired[0..3] = dG with dW_down, dh2 with
- * dW_up, dO with dW_o, dh1 with dW_qkv.  A shared launch has
- * tiles(first) + tiles(second) workgroups. */
+ * dW_up, dO with dW_o, dh1 with dW_qkv.  A shared launch of whole tiles has
+ * one workgroup per tile of either GEMM, or one per CU where it is
+ * persistent; where the first GEMM's few tiles are split along K it has one
+ * per slice of each, and the smallest pairs take 64 x 64 tiles. */
 typedef struct {
   int tiles, n_full, tail, splits, workgroups, threads;
 } pb_gemm_plan;
