@@ -1273,21 +1273,28 @@ static AttnSplit grid_split_plan(Dt dt, const AttnShape& a) {
 }
 
 // A split pays where the time it takes off the longest block exceeds its merge:
-// a launch (about 5 us; two, 8 us, in the backward) and the fp32 partials
-// written and read back (about 10 TB/s, they stay in the caches).  A tile takes
-// about 0.9 us in the forward, 1.05 us for dK/dV and 2.1 for dQ.  Measured with
-// the split and without (us, forward | backward):
+// a launch (about 4 us; two, 8 us, in the backward) and the fp32 partials
+// written and read back (8 to 10 TB/s, they stay in the caches).  A tile takes
+// 0.9 us and 0.004 us per column of head_dim in the forward, 1.05 us for dK/dV
+// and 2.1 for dQ: the forward's figures are fitted to 70 shapes of 1 to 31
+// heads, 101 to 5770 tokens, each timed both ways, and choose the slower side
+// nowhere by more than 5% but at 2 x 2183, 4 x 96, window 724 (25.5 / 22.0).
+// Measured with the split and without (us, forward | backward):
 //   2048 tokens, 12 heads of 128, full window   37 / 46   |
 //   4544, 3 x 128, full                         48 / 122  | 116 / 168
 //   1024, 8 x 128, full                         24 / 26   | 39 / 44
-//   512, 8 x 128, full                          14 / 16   | 30 / 26
+//   512, 8 x 128, full                          14.5 / 16 | 30 / 26
+//   4 x 1396, 7 x 96, full                      34 / 39   |
+//   2 x 1359, 16 x 96, full                     31.5 / 38.5 |
+//   2 x 677, 2 x 96, window 384                 13 / 14.5 | 25.6 / 22.6
 //   1024, 16 x 96, window 512                   22 / 17   | 45 / 29
 //   4096, 4 x 128, window 256                   23 / 15   | 48 / 28
 //   3 x 675, 16 x 128, window 300               25 / 18   |
 AttnSplit attn_split_plan(Dt dt, const AttnShape& a) {
   AttnSplit p = grid_split_plan(dt, a);
-  const double merge_us = 5.0 + 2.0 * attn_fwd_partial_bytes(a, p) / 1e7;
-  if (p.fwd_n > 1 && 0.9 * (p.fwd_tiles - p.fwd_chunk) < merge_us)
+  const double tile_us = 0.9 + 0.004 * a.head_dim;
+  const double merge_us = 4.0 + 2.0 * attn_fwd_partial_bytes(a, p) / 8e6;
+  if (p.fwd_n > 1 && tile_us * (p.fwd_tiles - p.fwd_chunk) < merge_us)
     p.fwd_chunk = kUnsplit, p.fwd_n = 1;
   return p;
 }

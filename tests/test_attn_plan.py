@@ -17,11 +17,26 @@ def ws(S, heads, d, W, batch=1):
     return size(pb.ATTN_WS_FORWARD) > 0, size(pb.ATTN_WS_BACKWARD) > size(pb.ATTN_WS_BACKWARD_MIN)
 
 
+@pytest.mark.parametrize("B,S,heads,d,W,fwd", [
+    # us split, us whole
+    (4, 1396, 7, 96, 1396, True),   # 34.0, 38.9
+    (2, 1359, 16, 96, 1359, True),  # 31.5, 38.5
+    (2, 677, 2, 96, 384, True),     # 12.9, 14.5
+    (2, 870, 10, 64, 870, True),    # 17.6, 21.6
+    (2, 1192, 12, 96, 238, False),  # 22.0, 13.9
+    (3, 675, 16, 128, 300, False),  # 24.4, 17.4
+    (1, 5770, 5, 128, 342, False),  # 30.7, 20.9
+])
+def test_split_plan_of_batches(B, S, heads, d, W, fwd):
+    assert ws(S, heads, d, W, B)[0] == fwd
+
+
 @pytest.mark.parametrize("S,heads,d,W,fwd,bwd", [
     (2048, 12, 128, 2048, True, False),  # the backward's two roles fill the chip
     (4544, 3, 128, 4544, True, True),
     (1024, 8, 128, 1024, True, True),
-    (512, 8, 128, 512, False, False),
+    # forward 14.5 us split, 15.9 whole; backward 30.6 and 25.7
+    (512, 8, 128, 512, True, False),
     (1024, 16, 96, 512, False, False),
     (4096, 4, 128, 256, False, False),
     (256, 4, 128, 96, False, False),
