@@ -1273,7 +1273,7 @@ static AttnSplit grid_split_plan(Dt dt, const AttnShape& a) {
 }
 
 // A split pays where the time it takes off the longest block exceeds its merge:
-// a launch (about 4 us; two, 8 us, in the backward) and the fp32 partials
+// a launch (about 3.5 us; two, 8 us, in the backward) and the fp32 partials
 // written and read back (8 to 10 TB/s, they stay in the caches).  A tile takes
 // 0.9 us and 0.004 us per column of head_dim in the forward, 1.05 us for dK/dV
 // and 2.1 for dQ: the forward's figures are fitted to 70 shapes of 1 to 31
@@ -1287,13 +1287,14 @@ static AttnSplit grid_split_plan(Dt dt, const AttnShape& a) {
 //   4 x 1396, 7 x 96, full                      34 / 39   |
 //   2 x 1359, 16 x 96, full                     31.5 / 38.5 |
 //   2 x 677, 2 x 96, window 384                 13 / 14.5 | 25.6 / 22.6
+//   3 x 510, 1 x 128, window 177                12.6 / 13.5 |
 //   1024, 16 x 96, window 512                   22 / 17   | 45 / 29
 //   4096, 4 x 128, window 256                   23 / 15   | 48 / 28
 //   3 x 675, 16 x 128, window 300               25 / 18   |
 AttnSplit attn_split_plan(Dt dt, const AttnShape& a) {
   AttnSplit p = grid_split_plan(dt, a);
   const double tile_us = 0.9 + 0.004 * a.head_dim;
-  const double merge_us = 4.0 + 2.0 * attn_fwd_partial_bytes(a, p) / 8e6;
+  const double merge_us = 3.5 + 2.0 * attn_fwd_partial_bytes(a, p) / 8e6;
   if (p.fwd_n > 1 && tile_us * (p.fwd_tiles - p.fwd_chunk) < merge_us)
     p.fwd_chunk = kUnsplit, p.fwd_n = 1;
   return p;

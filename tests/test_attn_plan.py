@@ -23,6 +23,7 @@ def ws(S, heads, d, W, batch=1):
     (2, 1359, 16, 96, 1359, True),  # 31.5, 38.5
     (2, 677, 2, 96, 384, True),     # 12.9, 14.5
     (2, 870, 10, 64, 870, True),    # 17.6, 21.6
+    (3, 510, 1, 128, 177, True),    # 12.6, 13.5
     (2, 1192, 12, 96, 238, False),  # 22.0, 13.9
     (3, 675, 16, 128, 300, False),  # 24.4, 17.4
     (1, 5770, 5, 128, 342, False),  # 30.7, 20.9
