@@ -148,17 +148,14 @@ PB_DEV float swap16_sum(float v) {
 // tanh|a| = (1 - e) / (1 + e), e = 2^(-2|a| log2 e), whose error against float64
 // measured slightly smaller there.
 //
-// Erf form: u Phi(u), derivative Phi(u) + u phi(u), Phi(u) = 0.5 (1 + erf(u /
-// sqrt 2)).  For results rounded to bf16, erfc(x) = (a1 t + .. + a5 t^5)
-// e^(-x^2), t = 1 / (1 + 0.3275911 x), x = |u| / sqrt 2 (Abramowitz and Stegun
-// 7.1.26, absolute error 1.5e-7): its e^(-x^2) = e^(-u^2 / 2) is the
-// derivative's too, and Phi needs no 1 - erf for negative u.  fp32 results
-// take the ROCm device erff.
+// Erf form: 0.5 u (1 + erf(u / sqrt 2)), by the ROCm device erff, for results of
+// either type.  (erfc by a five-term polynomial in 1 / (1 + p |u|) times
+// e^(-u^2 / 2) is cheaper, 744 us against 762 for the block of 2025 tokens, hidden
+// 2048, and has two to six times erff's error.)
 //
-// Measured with the row sums above in the epilogues (rotations instead of LDS
-// shuffles): a small block (256 tokens, hidden 512) 135.7 -> 122.1 us, the erf
-// block of 2025 tokens, hidden 2048 814 -> 789 us, the 175B share within noise
-// (its GEMMs run at the power limit).
+// Measured, the tanh form with the row sums above in the epilogues (rotations
+// instead of LDS shuffles): a small block (256 tokens, hidden 512) 135.7 -> 122.1
+// us, the 175B share within noise (its GEMMs run at the power limit).
 constexpr float kSqrt2OverPi = 0.7978845608028654f;
 constexpr float kGeluC = 0.044715f;
 constexpr float kInvSqrt2 = 0.7071067811865476f;
@@ -175,17 +172,6 @@ PB_DEV float gelu_sigmoid(float u, float u2) {
   const float e = __builtin_amdgcn_exp2f(u * __builtin_fmaf(c1 * kGeluC, u2, c1));
   return __builtin_amdgcn_rcpf(1.0f + e);
 }
-// Phi(u), and e^(-u^2 / 2).
-PB_DEV float normal_cdf(float u, float& ex) {
-  const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f * kInvSqrt2, fabsf(u), 1.0f));
-  ex = __builtin_amdgcn_exp2f(-0.5f * kLog2e * u * u);
-  float p = __builtin_fmaf(1.061405429f, t, -1.453152027f);
-  p = __builtin_fmaf(p, t, 1.421413741f);
-  p = __builtin_fmaf(p, t, -0.284496736f);
-  p = __builtin_fmaf(p, t, 0.254829592f);
-  const float half_erfc = 0.5f * p * t * ex;
-  return u < 0.0f ? half_erfc : 1.0f - half_erfc;
-}
 
 // T: the type the result is rounded to.
 template <typename T, bool TANH>
@@ -194,9 +180,6 @@ PB_DEV float gelu(float u) {
     return u * gelu_sigmoid(u, u * u);
   } else if constexpr (TANH) {
     return 0.5f * u * (1.0f + tanh_fast(kSqrt2OverPi * (u + kGeluC * u * u * u)));
-  } else if constexpr (sizeof(T) == 2) {
-    float ex;
-    return u * normal_cdf(u, ex);
   } else {
     return 0.5f * u * (1.0f + erff(u * kInvSqrt2));
   }
@@ -219,10 +202,6 @@ PB_DEV float gelu_grad(float u) {
     const float q = er * r * u;
     return __builtin_fmaf(q * u, (6.0f * kSqrt2OverPi * kGeluC) * u,
                           __builtin_fmaf(q, 2.0f * kSqrt2OverPi, s));
-  } else if constexpr (sizeof(T) == 2) {
-    float ex;
-    const float cdf = normal_cdf(u, ex);
-    return __builtin_fmaf(u * kInvSqrt2Pi, ex, cdf);
   } else {
     return 0.5f * (1.0f + erff(u * kInvSqrt2)) +
            u * kInvSqrt2Pi * __builtin_amdgcn_exp2f(-0.5f * kLog2e * u * u);

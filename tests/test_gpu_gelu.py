@@ -8,6 +8,8 @@ this dwarfs the value).  NaN stays NaN."""
 import numpy as np
 import pytest
 
+from paper_2402_15627_amd.inputs import round_to_bf16
+
 pytestmark = pytest.mark.gpu
 
 
@@ -66,3 +68,32 @@ def test_tanh_gelu_grad_of_every_value(tokens, hidden, tile):
     ref = _grad_reference(u[fin])
     over = np.abs(got[fin] - ref) - 0.5 * _step(ref) - 2.5e-7
     assert over.max() <= 0, (u[fin][over.argmax()], over.max())
+
+
+def test_erf_gelu_is_correctly_rounded():
+    """u in (-4, 8): there no float64 value lies closer to a rounding boundary
+    than the fp32 evaluation's error (device erff to an ulp), so each result is
+    the bf16 value nearest to it."""
+    import torch
+    from scipy.special import erfc
+    from paper_2402_15627_amd import pblock as pb
+    print("[gpu] GeLU erf", flush=True)
+    u, T, H = _all_bf16(), 8, 8
+    cfg = pb.make_config(1, T, H, 1, 64, u.size, 1, "bf16", 1e-5, False)
+    new = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    h, w_in, z, c = new(T, H), new(192 + u.size, H), new(T, 192 + u.size), new(T, 64 + u.size)
+    b_in = new(192 + u.size)
+    b_in[192:] = torch.from_numpy(u).cuda().to(torch.bfloat16)
+    n = pb.pblock_ag_in_proj_workspace_bytes(cfg, 1, 1)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda") if n else None
+    with pb.TpContext(1) as ctx:
+        pb.pblock_ag_in_proj(cfg, 1, 0, [h], h, w_in, b_in, z, c, 1, ws,
+                             torch.cuda.current_stream(), [torch.cuda.Stream()], ctx)
+    torch.cuda.synchronize()
+    got = c[:, 64:].float().cpu().numpy()
+    ok = (u > -4) & (u < 8) & (np.abs(u) > 1e-30)
+    v = u[ok].astype(np.float64)
+    want = round_to_bf16((v * 0.5 * erfc(-v / np.sqrt(2))).astype(np.float32))
+    for row in got:
+        assert np.array_equal(row[ok], want), u[ok][row[ok] != want]
+    assert np.isnan(got[:, np.isnan(u)]).all()
