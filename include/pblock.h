@@ -262,6 +262,18 @@ pb_status pblock_gemm_plan(pb_dtype dtype, int M, int N, int K,
                            pb_gemm_plan* plan);
 pb_status pblock_backward_pairs(const pb_config* cfg, int block, int* paired);
 
+/* How the pairs of pblock_backward_pairs launch (same block and order; host
+ * only) when the backward call is given a workspace of ws_bytes: apart, or
+ * together in whole 256 x 256 tiles, in 256 x 256 tiles with each of the first
+ * GEMM's cut into `splits` K-slices, or in 64 x 64 tiles.  splits is 1 unless
+ * the kind is PB_PAIR_SPLIT. */
+typedef enum { PB_PAIR_APART = 0, PB_PAIR_WHOLE, PB_PAIR_SPLIT, PB_PAIR_SMALL } pb_pair_kind;
+typedef struct {
+  int kind, splits;
+} pb_pair_launch;
+pb_status pblock_backward_launches(const pb_config* cfg, int block, size_t ws_bytes,
+                                   pb_pair_launch* launch);
+
 /* ---------------------------------------------------------- serial block
  * The standard pre-LN block that Eq. 2 replaces (Section 3.1, Eq. 1), for
  * comparison and for models that keep it:

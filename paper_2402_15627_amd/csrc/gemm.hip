@@ -917,7 +917,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_dma_pair(DmaGemm g1, in
 // The shared launch with every tile of the first GEMM cut into `splits`
 // K-slices, whose partial tiles splitk_reduce sums and finishes: a first GEMM of
 // few tiles and a long K would otherwise hold a handful of CUs long after the
-// second one's tiles are done (gemm_pair_splits).
+// second one's tiles are done (pair_splits).
 template <bool AK1, bool BK1, bool AK2, bool BK2>
 __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_dma_pair_split(DmaGemm g1, int tiles1,
                                                                         int splits,
@@ -1245,72 +1245,108 @@ void launch_queue_reset(int* queue, int n, hipStream_t s) {
   if (n > 0) queue_reset_kernel<<<1, 64, 0, s>>>(queue, n);
 }
 
-// Estimated end of the shared launch, in K-tile steps of one workgroup: n1
-// items of a steps and n2 of b on 256 CUs, the first started first; then, when
-// split, the sum of the slices (a launch, and the fp32 partial tiles written
-// and read back, about 1/16 of a step each).  Measured, backward of a block,
-// whole -> split tiles: 128 tokens, hidden 1024, FFN 4096 205 -> 72 us; 512,
-// 2048, 8192 367 -> 190 us; 1024, 4096, 16384 1059 -> 832 us; the serial block
-// of 2048 tokens, hidden 12288, 16 heads of 96 (dO + dW_o: 48 tiles of 192
-// K-tiles beside 288 of 32) 2675 -> 2609 us for the whole step.  2048 tokens
-// at hidden 4096 and above stay whole.
+// The end of a launch of n1 items of a and then n2 of b on kCUs CUs that take
+// items in this order.
+static double launch_end(long long n1, double a, long long n2, double b) {
+  // after the first items `early` CUs are free at t0 and `late` ones at t0 + a
+  const long long late = n1 % kCUs, early = kCUs - late;
+  const double t0 = (double)(n1 / kCUs) * a, t1 = late ? t0 + a : t0;
+  if (!late) return t0 + (double)((n2 + kCUs - 1) / kCUs) * b;
+  // the early CUs take `alone` rounds of the second items before the late ones
+  // join; from then on the two sides take their rounds in turn, late ones first
+  const long long alone = (long long)(a / b) + 1;
+  if (n2 <= alone * early)
+    return std::max(t1, t0 + (double)((n2 + early - 1) / early) * b);
+  const long long rest = n2 - alone * early, full = rest / kCUs, over = rest % kCUs;
+  const double e = t0 + (double)(alone + full) * b;
+  if (over == 0) return e;
+  return over <= late ? std::max(e, t1 + (double)(full + 1) * b) : e + b;
+}
+
+// delta formed by a launch of its own (dO and O read once; attn_delta_kernel),
+// where the pair's first GEMM forms it in its epilogue when it runs whole.
+static double delta_us(const GemmSpec& g) {
+  const double cols = (double)g.ep.delta_heads * g.ep.delta_hd;
+  return cols > 0 ? 3.5 + 4.0 * g.M * cols / 5.8e6 : 0.0;
+}
+
+// K-slices per tile of the pair's first GEMM, and the estimated time of the
+// shared launch in K-tile steps (kStepUs): the items' end in the order in which
+// they start, a whole or cut tile of the first GEMM its K-tiles, a tile of the
+// second one its own and 1.5 for its stores; when cut, 2.5% for the plain launch
+// (the persistent one evens out the XCDs), the partial tiles written and summed,
+// 1/17 of a step each, and delta's launch where a whole first GEMM would form it.
+// The second GEMM's tiles are never cut, so with a long T they bound the launch,
+// and cutting the first GEMM only delays them.  Chosen on the two pairs of 140
+// blocks of 64 to 8192 tokens, each timed whole and with 2 to 16 slices: what it
+// picks is nowhere slower than whole tiles (0.2% at most), and slower than the
+// best of all by 1% on average and by 10 to 12% in three pairs.
+// Measured, the pair whole -> cut: dh + dW_in at 512 tokens, hidden 2048, A 1024,
+// FFN 8192 205 -> 67 us; 1024, 4096, 2048, 16384 530 -> 337; 192, 8320, 8320,
+// 33280 1458 -> 656.  Left whole: dC + dW_out at 7296 tokens, hidden 2176, A 256,
+// FFN 1088 148 us (cut in two 197), dh + dW_in at 7744, 768, 768, 3072 176 (195)
+// and at 6336, 1152, 512, 2304 147 (202).
 static int pair_splits(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats, double* steps) {
   const int t1 = tiles_of(g1), t2 = tiles_of(g2), nk1 = g1.K / kBK, nk2 = g2.K / kBK;
   auto cost = [&](int s) {
-    const int n1 = t1 * s, a = (nk1 + s - 1) / s;
-    const double rounds = (double)((n1 + kCUs - 1) / kCUs) * a;
-    const double all = ((double)n1 * a + (double)t2 * nk2) / kCUs;
-    const double end = n1 + t2 <= kCUs ? std::max(a, nk2)
-                                       : std::max(rounds, all + 0.5 * std::min(a, nk2));
-    return s == 1 ? end : end + 4.0 + n1 / 16.0;
+    const double end = launch_end((long long)t1 * s, (nk1 + s - 1) / s, t2, nk2 + 1.5);
+    return s == 1 ? end : 1.025 * end + t1 * s / 17.0 + delta_us(g1) / kStepUs;
   };
   int best = 1;
-  for (int s = 2; s <= std::min(16, nk1); ++s)
-    if ((size_t)t1 * s * kBM * kBN <= ws_floats && cost(s) < cost(best)) best = s;
-  if (steps) *steps = cost(best) - (best > 1 ? 4.0 + t1 * best / 16.0 : 0);
+  double least = cost(1);
+  for (int s = 2; s <= std::min(16, nk1); ++s) {
+    if ((size_t)t1 * s * kBM * kBN > ws_floats) break;
+    const double c = cost(s);
+    if (c < least) best = s, least = c;
+  }
+  *steps = least;
   return best;
 }
-int gemm_pair_splits(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats) {
-  return pair_splits(g1, g2, ws_floats, nullptr);
-}
 
-// The shared launch in 64 x 64 tiles: against its end in 256 x 256 ones, as
-// gemm_small_wins.
-static bool pair_small_wins(const GemmSpec& g1, const GemmSpec& g2) {
-  double steps = 0;
-  const int splits = pair_splits(g1, g2, SIZE_MAX, &steps);
-  const double big = kTileUs + kStepUs * steps + (splits > 1 ? split_sum_us(tiles_of(g1) * splits) : 0);
+// The shared launch in 64 x 64 tiles (delta then in its own launch) against the
+// one in 256 x 256 tiles, whose launch, prologue and first epilogue cost 12 us.
+// On the same pairs the wrong side is picked by 12 to 23% in five, worst at 2176
+// tokens, hidden 512: dh + dW_in 59 us cut in two, 48 in 64 x 64 tiles.
+static bool pair_small_wins(const GemmSpec& g1, const GemmSpec& g2, double steps) {
+  const double big = 12.0 + kStepUs * steps;
   const double u1 = small_tile_us(g1.K, true), u2 = small_tile_us(g2.K, true);
   const int t1 = gemm_small_tiles(g1.M, g1.N), t2 = gemm_small_tiles(g2.M, g2.N);
   const double all = (t1 * u1 + t2 * u2) / kCUs + (t1 + t2 > kCUs ? 0.5 * std::min(u1, u2) : 0);
-  return 4.0 + std::max(all, std::max(u1, u2)) < 0.95 * big;
+  return 4.0 + delta_us(g1) + std::max(all, std::max(u1, u2)) < 0.95 * big;
 }
 
-bool gemm_pair_whole(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats) {
-  return !pair_small_wins(g1, g2) && gemm_pair_splits(g1, g2, ws_floats) == 1;
+GemmPairLaunch gemm_pair_launch(Dt dt, const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats) {
+  if (!gemm_pair_supported(dt, g1, g2)) return {GemmPairKind::Apart, 1};
+  double steps;
+  // (64 x 64 tiles or not depends on the sizes alone, not on the space at hand)
+  int s = pair_splits(g1, g2, SIZE_MAX, &steps);
+  if (pair_small_wins(g1, g2, steps)) return {GemmPairKind::Small, 1};
+  if (s > 1 && (size_t)tiles_of(g1) * s * kBM * kBN > ws_floats)
+    s = pair_splits(g1, g2, ws_floats, &steps);
+  return {s > 1 ? GemmPairKind::Split : GemmPairKind::Whole, s};
 }
 
 size_t gemm_pair_split_floats(Dt dt, const GemmSpec& g1, const GemmSpec& g2) {
-  if (!gemm_pair_supported(dt, g1, g2) || pair_small_wins(g1, g2)) return 0;
-  const int s = gemm_pair_splits(g1, g2, SIZE_MAX);
-  return s > 1 ? (size_t)tiles_of(g1) * s * kBM * kBN : 0;
+  const GemmPairLaunch l = gemm_pair_launch(dt, g1, g2, SIZE_MAX);
+  return l.kind == GemmPairKind::Split ? (size_t)tiles_of(g1) * l.splits * kBM * kBN : 0;
 }
 
 bool launch_gemm_pair(Dt dt, const GemmSpec& g1, const GemmSpec& g2, int* queue, float* split_ws,
                       size_t split_ws_floats, hipStream_t s) {
-  if (!gemm_pair_supported(dt, g1, g2)) return false;
+  const GemmPairLaunch l = gemm_pair_launch(dt, g1, g2, split_ws ? split_ws_floats : 0);
+  if (l.kind == GemmPairKind::Apart) return false;
   auto desc = [](const GemmSpec& g) {
     return DmaGemm{(const bf16*)g.A, g.lda, (const bf16*)g.B, g.ldb, g.M, g.N, g.K, g.ep};
   };
   const DmaGemm d1 = desc(g1), d2 = desc(g2);
   const int t1 = tiles_of(g1), t2 = tiles_of(g2);
   const size_t lds = 4 * (size_t)kTileBytes;
-  if (pair_small_wins(g1, g2)) {
+  if (l.kind == GemmPairKind::Small) {
     launch_gemm_small_pair(g1, g2, s);
     return true;
   }
-  const int splits = split_ws ? gemm_pair_splits(g1, g2, split_ws_floats) : 1;
-  if (splits > 1) {
+  if (l.kind == GemmPairKind::Split) {
+    const int splits = l.splits;
     gemm_bf16_dma_pair_split<true, false, false, false>
         <<<t1 * splits + t2, kThreads, lds, s>>>(d1, t1, splits, split_ws, d2, t2);
     static_assert(tile_group(Epi::StoreF32) == tile_group(Epi::LnGrad) &&

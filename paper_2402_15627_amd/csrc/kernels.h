@@ -130,7 +130,8 @@ struct EpiArgs {
   // also delta[(b heads + h) seq + t] = sum over head h's columns of
   // out[m, n] o_rows[m * ld_o_rows + n] for m = b seq + t, n < split, with
   // out rounded to the activation type first; head_dim 64 or 128, split and
-  // the tile's column blocks aligned to heads.
+  // the tile's column blocks aligned to heads.  delta_hd is set wherever a
+  // whole launch may form delta, delta itself where it does.
   const void* o_rows = nullptr;
   int ld_o_rows = 0;
   float* delta = nullptr;
@@ -177,7 +178,7 @@ void launch_gemm(Dt dt, Epi epi, bool a_kcontig, bool b_kcontig, const void* A, 
 // Two independent GEMMs in one launch: the first one's tiles are started first
 // (give it the longer K), and the second one's tiles fill the CUs the first
 // leaves idle.  Where the first one's few long tiles would outlast the launch
-// they are split along K (gemm_pair_splits), as launch_gemm splits, and a
+// they are split along K (gemm_pair_launch), as launch_gemm splits, and a
 // second kernel sums the slices.  Supported: bf16, K multiples of
 // 64 and operands the LDS-DMA path takes, with the first GEMM A K-contiguous,
 // B MN-contiguous and a DgeluSplit or LnGrad epilogue, the second both
@@ -213,13 +214,16 @@ int gemm_small_tiles(int M, int N);
 int gemm_small_threads();
 void launch_gemm_small(const GemmSpec& g, hipStream_t s);
 void launch_gemm_small_pair(const GemmSpec& g1, const GemmSpec& g2, hipStream_t s);
-// K-slices per tile of the first GEMM in the shared launch of a supported pair,
-// given ws_floats of space for partial tiles (1: whole tiles).
-int gemm_pair_splits(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats);
-// Whether a supported pair's launch computes whole 256 x 256 tiles (neither
-// split nor a small grid's): it then takes a queue, and the first GEMM's
-// epilogue forms delta when asked to.
-bool gemm_pair_whole(const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats);
+// How a pair launches, given ws_floats of space for partial tiles: apart, or in
+// one launch of 256 x 256 tiles (it then takes a queue, and the first GEMM's
+// epilogue forms delta when asked to), of 256 x 256 tiles with the first GEMM's
+// cut into `splits` K-slices, or of 64 x 64 tiles.
+enum class GemmPairKind { Apart, Whole, Split, Small };
+struct GemmPairLaunch {
+  GemmPairKind kind;
+  int splits;
+};
+GemmPairLaunch gemm_pair_launch(Dt dt, const GemmSpec& g1, const GemmSpec& g2, size_t ws_floats);
 size_t gemm_pair_split_floats(Dt dt, const GemmSpec& g1, const GemmSpec& g2);
 bool launch_gemm_pair(Dt dt, const GemmSpec& g1, const GemmSpec& g2, int* queue, float* split_ws,
                       size_t split_ws_floats, hipStream_t s);

@@ -138,6 +138,16 @@ void* at(void* base, long long elems, size_t esz) { return (char*)base + (size_t
 // place for the launches and for pblock_backward_pairs, so that the query
 // reports the pairing the launches make.  Null operands and default epilogue
 // arguments describe the shapes alone.
+// The attention backward's row terms may be formed in the epilogue of the GEMM
+// whose first A columns are dO, as they leave the accumulators, instead of
+// re-reading dO and O in a launch of their own: heads of 64 or 128 columns
+// whose blocks align with the epilogue's 128-column wave blocks.
+void offer_delta(pb::GemmSpec& g, const Dims& d) {
+  if ((d.d != 64 && d.d != 128) || d.A % 128) return;
+  g.ep.delta_seq = (int)d.S;
+  g.ep.delta_heads = (int)d.heads;
+  g.ep.delta_hd = (int)d.d;
+}
 struct ParallelBwdGemms {
   pb::GemmSpec dc, dw_out, dh, dw_in;
 };
@@ -147,7 +157,7 @@ ParallelBwdGemms parallel_bwd_gemms(const Dims& d, const void* dy, const void* w
                                     const pb::EpiArgs& e_dwo, const pb::EpiArgs& e_dh,
                                     const pb::EpiArgs& e_dwi) {
   const int T = (int)d.T, H = (int)d.H, N_in = (int)d.N_in, K_out = (int)d.K_out;
-  return {
+  ParallelBwdGemms g = {
       // dC = dy W_out (B MN-contiguous)
       {pb::Epi::DgeluSplit, true, false, dy, H, w_out, K_out, T, K_out, H, e_dc},
       // dW_out = dy^T C (contraction over tokens)
@@ -156,6 +166,8 @@ ParallelBwdGemms parallel_bwd_gemms(const Dims& d, const void* dy, const void* w
       {pb::Epi::LnGrad, true, false, dz, N_in, w_in, H, T, H, N_in, e_dh},
       // dW_in = dZ^T h
       {pb::Epi::StoreF32, false, false, dz, N_in, h, H, N_in, H, T, e_dwi}};
+  offer_delta(g.dc, d);
+  return g;
 }
 
 struct SerialBwdGemms {
@@ -173,7 +185,7 @@ SerialBwdGemms serial_bwd_gemms(const Dims& d, const SerialBwdOperands& o,
             K_out = (int)d.K_out;
   const size_t e = d.esz;
   auto off = [&](const void* p, long long n) { return p ? at(p, n, e) : nullptr; };
-  return {
+  SerialBwdGemms g = {
       // dG = dy W_down
       {pb::Epi::DgeluSplit, true, false, o.dy, H, off(o.w_out, A), K_out, T, F, H, e_dg},
       // dW_down = dy^T G
@@ -191,7 +203,13 @@ SerialBwdGemms serial_bwd_gemms(const Dims& d, const SerialBwdOperands& o,
       {pb::Epi::LnGrad, true, false, o.dz, N_in, o.w_in, H, T, H, 3 * A, e_dh1},
       // dW_qkv = dQKV^T h1
       {pb::Epi::StoreF32, false, false, o.dz, N_in, o.h1, H, 3 * A, H, T, e_wq}};
+  offer_delta(g.d_o, d);
+  return g;
 }
+bool whole_pair(pb::Dt dt, const pb::GemmSpec& g1, const pb::GemmSpec& g2, size_t split_f) {
+  return pb::gemm_pair_launch(dt, g1, g2, split_f).kind == pb::GemmPairKind::Whole;
+}
+
 // Optional space for split work: the GEMMs' tail-split partial tiles and the
 // attention kernels' chunk partials.  They are never live at the same time,
 // so one region serves both.
@@ -338,6 +356,12 @@ SerialBwdLayout serial_bwd_layout(const Dims& d) {
   L.split = take(serial_split_bwd(d, d.esz == 2 ? pb::Dt::BF16 : pb::Dt::F32));
   L.total = o;
   return L;
+}
+
+// Floats of the optional split region that a backward workspace of ws_bytes holds.
+template <typename Layout>
+size_t bwd_split_floats(const Layout& W, size_t ws_bytes) {
+  return ws_bytes >= W.total ? (W.total - W.split) / 4 : 0;
 }
 
 pb_status check_ptr(const void* p, const char* name) {
@@ -540,26 +564,45 @@ pb_status pblock_gemm_plan(pb_dtype dtype, int M, int N, int K, pb_gemm_plan* pl
   return PB_OK;
 }
 
-pb_status pblock_backward_pairs(const pb_config* cfg, int block, int* paired) {
+pb_status pblock_backward_launches(const pb_config* cfg, int block, size_t ws_bytes,
+                                   pb_pair_launch* launch) {
   PB_CHECK(check_config(cfg));
-  if (!paired) return fail(PB_ERR_INVALID_ARG, "paired is NULL");
+  if (!launch) return fail(PB_ERR_INVALID_ARG, "launch is NULL");
   if (block != 0 && block != 1) return fail(PB_ERR_INVALID_ARG, "block=%d must be 0 or 1", block);
   const Dims d = dims_of(cfg);
   const pb::Dt dt = dt_of(cfg);
   const pb::EpiArgs none;
+  auto put = [&](int i, const pb::GemmSpec& g1, const pb::GemmSpec& g2, size_t split_f) {
+    const pb::GemmPairLaunch l = pb::gemm_pair_launch(dt, g1, g2, split_f);
+    launch[i].kind = (int)l.kind;
+    launch[i].splits = l.splits;
+  };
   if (block == 0) {
+    const size_t f = bwd_split_floats(bwd_layout(d), ws_bytes);
     const ParallelBwdGemms g = parallel_bwd_gemms(d, nullptr, nullptr, nullptr, nullptr, nullptr,
                                                   nullptr, none, none, none, none);
-    paired[0] = pb::gemm_pair_supported(dt, g.dc, g.dw_out);
-    paired[1] = pb::gemm_pair_supported(dt, g.dh, g.dw_in);
+    put(0, g.dc, g.dw_out, f);
+    put(1, g.dh, g.dw_in, f);
   } else {
+    const size_t f = bwd_split_floats(serial_bwd_layout(d), ws_bytes);
     const SerialBwdGemms g =
         serial_bwd_gemms(d, SerialBwdOperands{}, none, none, none, none, none, none, none, none);
-    paired[0] = pb::gemm_pair_supported(dt, g.dg, g.dw_down);
-    paired[1] = pb::gemm_pair_supported(dt, g.dh2, g.dw_up);
-    paired[2] = pb::gemm_pair_supported(dt, g.d_o, g.dw_o);
-    paired[3] = pb::gemm_pair_supported(dt, g.dh1, g.dw_qkv);
+    put(0, g.dg, g.dw_down, f);
+    put(1, g.dh2, g.dw_up, f);
+    put(2, g.d_o, g.dw_o, f);
+    put(3, g.dh1, g.dw_qkv, f);
   }
+  return PB_OK;
+}
+
+pb_status pblock_backward_pairs(const pb_config* cfg, int block, int* paired) {
+  if (!paired) {
+    PB_CHECK(check_config(cfg));
+    return fail(PB_ERR_INVALID_ARG, "paired is NULL");
+  }
+  pb_pair_launch l[4];
+  PB_CHECK(pblock_backward_launches(cfg, block, 0, l));
+  for (int i = 0; i < (block == 0 ? 2 : 4); ++i) paired[i] = l[i].kind != PB_PAIR_APART;
   return PB_OK;
 }
 
@@ -625,7 +668,7 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x, const void*
   float* part = (float*)(wb + W.part);
   int* queue = (int*)(wb + W.queue);
   float* split_ws = (float*)(wb + W.split);
-  const size_t split_f = ws_bytes >= W.total ? (W.total - W.split) / 4 : 0;
+  const size_t split_f = bwd_split_floats(W, ws_bytes);
   const int T = (int)d.T, H = (int)d.H, A = (int)d.A, N_in = (int)d.N_in, K_out = (int)d.K_out;
   (void)ln_beta;
   (void)b_in;
@@ -670,26 +713,19 @@ pb_status pblock_backward_timed(const pb_config* cfg, const void* x, const void*
                     g.ep, split_ws, split_f, stream);
   };
   const bool pair_out = pb::gemm_pair_supported(dt, g_dc, g_dwo);
-  // The attention backward's row terms delta = rowsum(dO * O) per head are
-  // formed in dC's epilogue (the shared launch's LDS-staged path), where dO
-  // leaves the accumulators, instead of re-reading dO and O in a launch of
-  // their own: heads of 64 or 128 columns whose blocks align with the
-  // epilogue's 128-column wave blocks.
-  const bool whole_out = pair_out && pb::gemm_pair_whole(g_dc, g_dwo, split_f);
-  const bool delta_in_dc = whole_out && (d.d == 64 || d.d == 128) && A % 128 == 0;
+  const bool whole_out = whole_pair(dt, g_dc, g_dwo, split_f);
+  // delta = rowsum(dO * O) per head in dC's epilogue (see offer_delta)
+  const bool delta_in_dc = whole_out && g_dc.ep.delta_hd;
   // db_in = sum over tokens of dZ: the row sums of dW_in's A operand (dZ^T),
   // formed by the first tile column of dW_in, in the shared launch or alone
   const bool pair_in = pb::gemm_pair_supported(dt, g_dh, g_dwi);
-  const bool whole_in = pair_in && pb::gemm_pair_whole(g_dh, g_dwi, split_f);
+  const bool whole_in = whole_pair(dt, g_dh, g_dwi, split_f);
   const bool db_in_fused = pair_in || pb::gemm_rowsum_supported(dt, g_dwi, split_f);
   if (db_in_fused) G.dw_in.ep.rowsum = db_in;
   if (delta_in_dc) {
     G.dc.ep.o_rows = c;  // O = C[:, :A]
     G.dc.ep.ld_o_rows = K_out;
     G.dc.ep.delta = delta;
-    G.dc.ep.delta_seq = (int)d.S;
-    G.dc.ep.delta_heads = (int)d.heads;
-    G.dc.ep.delta_hd = (int)d.d;
   }
   {
     StepScope sc(step_ev, PB_STEP_DC, stream);  // with dW_out when they share a launch
@@ -1083,7 +1119,7 @@ pb_status pblock_serial_backward(const pb_config* cfg, const void* x, const void
   float* part = (float*)(wb + W.part);
   int* queue = (int*)(wb + W.queue);
   float* split_ws = (float*)(wb + W.split);
-  const size_t split_f = ws_bytes >= W.total ? (W.total - W.split) / 4 : 0;
+  const size_t split_f = bwd_split_floats(W, ws_bytes);
   const int T = (int)d.T, H = (int)d.H, A = (int)d.A, F = (int)d.F, N_in = (int)d.N_in,
             K_out = (int)d.K_out;
   const int nblk = pb::ln_backward_chunks(T);
@@ -1154,16 +1190,11 @@ pb_status pblock_serial_backward(const pb_config* cfg, const void* x, const void
     G.dw_up.ep.rowsum = db_in + 3LL * A;
     G.dw_qkv.ep.rowsum = db_in;
   }
-  const bool delta_in_do = pb::gemm_pair_supported(dt, G.d_o, G.dw_o) &&
-                           pb::gemm_pair_whole(G.d_o, G.dw_o, split_f) &&
-                           (d.d == 64 || d.d == 128) && A % 128 == 0;
+  const bool delta_in_do = whole_pair(dt, G.d_o, G.dw_o, split_f) && G.d_o.ep.delta_hd;
   if (delta_in_do) {
     G.d_o.ep.o_rows = c;  // O = C[:, :A]
     G.d_o.ep.ld_o_rows = K_out;
     G.d_o.ep.delta = delta;
-    G.d_o.ep.delta_seq = (int)d.S;
-    G.d_o.ep.delta_heads = (int)d.heads;
-    G.d_o.ep.delta_hd = (int)d.d;
   }
   auto run = [&](const pb::GemmSpec& g) {
     pb::launch_gemm(dt, g.epi, g.a_kcontig, g.b_kcontig, g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K,
@@ -1174,11 +1205,11 @@ pb_status pblock_serial_backward(const pb_config* cfg, const void* x, const void
   // shared launches of whole tiles are persistent, each with its own queue
   // heads, zeroed here
   static_assert(kBwdQueueSets >= 4, "one queue per shared launch");
-  auto whole_pair = [&](const pb::GemmSpec& g, const pb::GemmSpec& wg) {
-    return pb::gemm_pair_supported(dt, g, wg) && pb::gemm_pair_whole(g, wg, split_f);
+  auto whole = [&](const pb::GemmSpec& g, const pb::GemmSpec& wg) {
+    return whole_pair(dt, g, wg, split_f);
   };
-  if (whole_pair(G.dg, G.dw_down) || whole_pair(G.dh2, G.dw_up) || whole_pair(G.d_o, G.dw_o) ||
-      whole_pair(G.dh1, G.dw_qkv))
+  if (whole(G.dg, G.dw_down) || whole(G.dh2, G.dw_up) || whole(G.d_o, G.dw_o) ||
+      whole(G.dh1, G.dw_qkv))
     pb::launch_queue_reset(queue, 4 * pb::kQueueInts, stream);
   int n_pairs = 0;
   auto run_with = [&](const pb::GemmSpec& g, const pb::GemmSpec& wg) {

@@ -23,6 +23,7 @@ WS_FORWARD_WITH_STASH, WS_BACKWARD, WS_FORWARD = 0, 1, 2
 ATTN_WS_FORWARD, ATTN_WS_BACKWARD_MIN, ATTN_WS_BACKWARD = 0, 1, 2
 STATUS = {0: "PB_OK", 1: "PB_ERR_INVALID_ARG", 2: "PB_ERR_UNSUPPORTED", 3: "PB_ERR_WORKSPACE",
           4: "PB_ERR_HIP"}
+PAIR_KINDS = ("apart", "whole", "split", "small")  # pb_pair_kind
 SAVED_REGIONS = ("h", "z", "c", "mean", "rstd", "lse")
 WORKSPACE_REGIONS = ("d_o", "dz", "dh", "delta")
 SERIAL_SAVED_REGIONS = ("h1", "z", "c", "mean1", "rstd1", "lse", "x1", "h2", "mean2", "rstd2")
@@ -34,6 +35,7 @@ EXPORTS = (
     "pblock_forward", "pblock_backward", "pblock_swattn_forward",
     "pblock_swattn_workspace_bytes", "pblock_swattn_backward", "pblock_forward_timed",
     "pblock_backward_timed", "pblock_gemm_plan", "pblock_backward_pairs",
+    "pblock_backward_launches",
     "pblock_tp_context_create", "pblock_tp_context_destroy",
     "pblock_status_string", "pblock_last_error", "pblock_serial_saved_bytes",
     "pblock_serial_saved_offsets", "pblock_serial_workspace_bytes", "pblock_serial_forward",
@@ -66,6 +68,11 @@ class GemmPlan(ctypes.Structure):
     """pb_gemm_plan."""
     _fields_ = [("tiles", c_int), ("n_full", c_int), ("tail", c_int), ("splits", c_int),
                 ("workgroups", c_int), ("threads", c_int)]
+
+
+class PairLaunch(ctypes.Structure):
+    """pb_pair_launch."""
+    _fields_ = [("kind", c_int), ("splits", c_int)]
 
 
 class LambConfig(ctypes.Structure):
@@ -129,6 +136,7 @@ def load_library(path: str = LIB_PATH):
                                           P, c_size_t, P, POINTER(StepEvents)]),
         "pblock_gemm_plan": (c_int, [c_int, c_int, c_int, c_int, POINTER(GemmPlan)]),
         "pblock_backward_pairs": (c_int, [cfgp, c_int, POINTER(c_int)]),
+        "pblock_backward_launches": (c_int, [cfgp, c_int, c_size_t, POINTER(PairLaunch)]),
         "pblock_tp_context_create": (c_int, [c_int, POINTER(c_void_p)]),
         "pblock_tp_context_destroy": (None, [P]),
         "pblock_status_string": (ctypes.c_char_p, [c_int]),
@@ -288,6 +296,20 @@ def pblock_backward_pairs(cfg: PbConfig, block: str = "parallel") -> tuple:
     _check(load_library().pblock_backward_pairs(ctypes.byref(cfg), 0 if block == "parallel" else 1,
                                                 out))
     return tuple(bool(v) for v in out)
+
+
+def pblock_backward_launches(cfg: PbConfig, block: str = "parallel", ws_bytes=None) -> tuple:
+    """How each pair of pblock_backward_pairs launches, as (kind, splits) with
+    kind of PAIR_KINDS, given a backward workspace of ws_bytes (default: the
+    full one)."""
+    parallel = block == "parallel"
+    if ws_bytes is None:
+        size = pblock_workspace_bytes if parallel else pblock_serial_workspace_bytes
+        ws_bytes = size(cfg, WS_BACKWARD)
+    out = (PairLaunch * (2 if parallel else 4))()
+    _check(load_library().pblock_backward_launches(ctypes.byref(cfg), 0 if parallel else 1,
+                                                   ws_bytes, out))
+    return tuple((PAIR_KINDS[v.kind], v.splits) for v in out)
 
 
 class TpContext:
