@@ -393,6 +393,14 @@ typedef struct pb_tp_context pb_tp_context;
 pb_status pblock_tp_context_create(int tp, pb_tp_context** ctx);
 void pblock_tp_context_destroy(pb_tp_context* ctx);
 
+/* How the pipelined calls below copy a shard or chunk from src to dst (host
+ * only): *by_kernel is 1 for a copy kernel, used where both are memory that
+ * this process allocated on the context's device, and 0 for the DMA engines
+ * (peers' memory opened by IPC handles, and anything else).  The copies of one
+ * launch on one comm stream take the kernel only where it holds for all. */
+pb_status pblock_tp_copies_by_kernel(const pb_tp_context* ctx, const void* src,
+                                     const void* dst, int* by_kernel);
+
 /* ------------------------------------------- in-projection + all-gather
  * Section 3.2 ("Overlapping in tensor/sequence parallelism", Fig. 3):
  * under sequence parallelism the LayerNorm output h is sharded along the

@@ -3,6 +3,8 @@
 // sequence of the forward and backward passes on the caller's stream.
 #include "pblock.h"
 
+#include <dlfcn.h>
+#include <hsa/hsa_ext_amd.h>
 #include <math.h>
 
 #include <cmath>
@@ -1351,25 +1353,47 @@ bool tp_args_ok(const pb_config* cfg, int tp, int per_launch) {
          per_launch <= tp && dims_of(cfg).T % tp == 0;
 }
 
+// Whether p lies in device memory that this process allocated on `device`.
+// hipPointerGetAttributes alone does not say so: a pointer opened from another
+// process's IPC handle reads as ordinary device memory there, and nothing ties
+// the device it names to the GPU that holds it.  The runtime below HIP keeps the
+// kind of the allocation (its own, IPC, imported by dmabuf), so that is asked
+// first, through the copy of it that HIP itself runs on.
+bool own_memory(const void* p, int device) {
+  typedef decltype(&hsa_amd_pointer_info) InfoFn;
+  static const InfoFn pointer_info = [] {
+    hipError_t (*hip_fn)(hipPointerAttribute_t*, const void*) = hipPointerGetAttributes;
+    Dl_info lib;
+    void* hip = dladdr((void*)hip_fn, &lib) ? dlopen(lib.dli_fname, RTLD_LAZY | RTLD_NOLOAD)
+                                            : nullptr;
+    return hip ? (InfoFn)dlsym(hip, "hsa_amd_pointer_info") : nullptr;
+  }();
+  if (!pointer_info) return false;
+  hsa_amd_pointer_info_t info;
+  memset(&info, 0, sizeof info);
+  info.size = sizeof info;
+  if (pointer_info(p, &info, nullptr, nullptr, nullptr) != HSA_STATUS_SUCCESS ||
+      info.type != HSA_EXT_POINTER_TYPE_HSA)
+    return false;
+  // (an error left by earlier work stays for the caller to see)
+  if (hipPeekAtLastError() != hipSuccess) return false;
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == device;
+}
+
 // The copies of one launch group on one comm stream.  Between buffers of this
-// GPU a kernel copies them all (memory-bound, ~4 TB/s; the DMA engines move
-// ~150 GB/s between local buffers, which then set the pace of the whole
-// pipeline: 2048 x 12288 bf16 rows over 8 ranks 707 -> 576 us for the
-// all-gather into the in-projection, 599 -> 508 us for the out-projection
-// into the reduce-scatter).  A list with a buffer of another GPU goes to the
-// DMA engines, which need no mapping of it here and leave the CUs to the GEMM.
-pb_status copy_on(const pb::CopyList& list, size_t bytes, int device, hipStream_t s) {
-  auto local = [&](const void* p) {
-    hipPointerAttribute_t a;
-    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
-      (void)hipGetLastError();  // not an error of this call: the copy reports its own
-      return false;
-    }
-    return a.type == hipMemoryTypeDevice && a.device == device;
-  };
-  bool all = true;
-  for (int i = 0; i < list.n; ++i) all = all && local(list.src[i]) && local(list.dst[i]);
-  if (all) {
+// process on this GPU (`own`) a kernel copies them all (memory-bound, ~4 TB/s;
+// the DMA engines move ~150 GB/s between local buffers, which then set the pace
+// of the whole pipeline: 2048 x 12288 bf16 rows over 8 ranks 707 -> 576 us for
+// the all-gather into the in-projection, 599 -> 508 us for the out-projection
+// into the reduce-scatter).  A list with any other buffer, a peer's opened by an
+// IPC handle say, goes to the DMA engines, which leave the CUs to the GEMM.
+pb_status copy_on(const pb::CopyList& list, bool own, size_t bytes, hipStream_t s) {
+  if (own) {
     pb::launch_copies(list, bytes, s);
     return PB_OK;
   }
@@ -1380,6 +1404,17 @@ pb_status copy_on(const pb::CopyList& list, size_t bytes, int device, hipStream_
   return PB_OK;
 }
 
+}  // namespace
+
+pb_status pblock_tp_copies_by_kernel(const pb_tp_context* ctx, const void* src, const void* dst,
+                                     int* by_kernel) {
+  if (!ctx || !src || !dst || !by_kernel)
+    return fail(PB_ERR_INVALID_ARG, "ctx, src, dst or by_kernel is NULL");
+  *by_kernel = own_memory(src, ctx->device) && own_memory(dst, ctx->device);
+  return PB_OK;
+}
+
+namespace {
 // All-gather pipelined into a row-parallel GEMM: the shards are copied into
 // `gathered` on the comm streams in ring order from `rank` (the k-th on
 // comm_streams[k % n_comm]); gemm_rows(j0, n) computes the GEMM over the
@@ -1399,8 +1434,12 @@ pb_status ag_pipeline(int tp, int rank, const void* const* shards, void* gathere
   // shard already in place needs no wait (cross-stream waits cost ~0.1 ms
   // per call when every shard went through them).
   bool any_copy = false;
+  bool own[kAgMaxTp];  // per shard, asked before this call's first launch
   for (int j = 0; j < tp; ++j) any_copy = any_copy || !in_place(j);
   if (any_copy) {
+    const bool own_dst = own_memory(gathered, ev.device);
+    for (int j = 0; j < tp; ++j)
+      own[j] = own_dst && !in_place(j) && own_memory(shards[j], ev.device);
     // the copies start after the work already on `stream` (which may produce
     // the local shard)
     if (!ok(hipEventRecord(ev.start, stream))) return fail(PB_ERR_HIP, "hipEventRecord failed");
@@ -1425,16 +1464,18 @@ pb_status ag_pipeline(int tp, int rank, const void* const* shards, void* gathere
   for (int n = 0; n < groups; ++n)
     for (int i = 0; i < n_comm; ++i) {
       pb::CopyList list{};
+      bool all_own = true;
       int last = -1;
       for (int k = first[n]; k < first[n + 1]; ++k) {
         const int j = (rank + k) % tp;
         if (k % n_comm != i || in_place(j)) continue;
         list.src[list.n] = shards[j];
         list.dst[list.n++] = (char*)gathered + (size_t)j * shard_bytes;
+        all_own = all_own && own[j];
         last = k;
       }
       if (!list.n) continue;
-      PB_CHECK(copy_on(list, shard_bytes, ev.device, comm_streams[i]));
+      PB_CHECK(copy_on(list, all_own, shard_bytes, comm_streams[i]));
       landed[n][i] = ev.landed[last];
       if (!ok(hipEventRecord(landed[n][i], comm_streams[i])))
         return fail(PB_ERR_HIP, "hipEventRecord failed");
@@ -1467,6 +1508,17 @@ pb_status rs_pipeline(int tp, int rank, const void* partial, void* const* dst, s
   auto ok = [](hipError_t e) { return e == hipSuccess; };
   int group = 0;
   bool used[kAgMaxComm] = {};
+  auto in_place = [&](int j) {
+    return dst[j] == (const char*)partial + (size_t)j * chunk_bytes;
+  };
+  // per chunk, asked before this call's first launch
+  bool own[kAgMaxTp], any_copy = false;
+  for (int j = 0; j < tp; ++j) any_copy = any_copy || !in_place(j);
+  if (any_copy) {
+    const bool own_src = own_memory(partial, ev.device);
+    for (int j = 0; j < tp; ++j)
+      own[j] = own_src && !in_place(j) && own_memory(dst[j], ev.device);
+  }
   for (int k0 = 0; k0 < tp; k0 += per_launch, ++group) {
     const int k1 = std::min(tp, k0 + per_launch);
     const int j0 = (rank + 1 + k0) % tp, n = k1 - k0;
@@ -1480,13 +1532,14 @@ pb_status rs_pipeline(int tp, int rank, const void* partial, void* const* dst, s
     bool recorded = false;
     for (int i = 0; i < n_comm; ++i) {
       pb::CopyList list{};
+      bool all_own = true;
       for (int k = k0; k < k1; ++k) {
         const int j = (rank + 1 + k) % tp;
-        const char* src = (const char*)partial + (size_t)j * chunk_bytes;
         // a chunk in place has nothing to send or wait for
-        if (k % n_comm != i || dst[j] == src) continue;
-        list.src[list.n] = src;
+        if (k % n_comm != i || in_place(j)) continue;
+        list.src[list.n] = (const char*)partial + (size_t)j * chunk_bytes;
         list.dst[list.n++] = dst[j];
+        all_own = all_own && own[j];
       }
       if (!list.n) continue;
       if (!recorded && !ok(hipEventRecord(ev.computed[group], stream)))
@@ -1495,7 +1548,7 @@ pb_status rs_pipeline(int tp, int rank, const void* partial, void* const* dst, s
       hipStream_t cs = comm_streams[i];
       if (!ok(hipStreamWaitEvent(cs, ev.computed[group], 0)))
         return fail(PB_ERR_HIP, "hipStreamWaitEvent failed");
-      PB_CHECK(copy_on(list, chunk_bytes, ev.device, cs));
+      PB_CHECK(copy_on(list, all_own, chunk_bytes, cs));
       used[i] = true;
     }
   }

@@ -36,7 +36,7 @@ EXPORTS = (
     "pblock_swattn_workspace_bytes", "pblock_swattn_backward", "pblock_forward_timed",
     "pblock_backward_timed", "pblock_gemm_plan", "pblock_backward_pairs",
     "pblock_backward_launches",
-    "pblock_tp_context_create", "pblock_tp_context_destroy",
+    "pblock_tp_context_create", "pblock_tp_context_destroy", "pblock_tp_copies_by_kernel",
     "pblock_status_string", "pblock_last_error", "pblock_serial_saved_bytes",
     "pblock_serial_saved_offsets", "pblock_serial_workspace_bytes", "pblock_serial_forward",
     "pblock_serial_backward", "pblock_lamb_workspace_bytes", "pblock_lamb_step",
@@ -138,6 +138,7 @@ def load_library(path: str = LIB_PATH):
         "pblock_backward_pairs": (c_int, [cfgp, c_int, POINTER(c_int)]),
         "pblock_backward_launches": (c_int, [cfgp, c_int, c_size_t, POINTER(PairLaunch)]),
         "pblock_tp_context_create": (c_int, [c_int, POINTER(c_void_p)]),
+        "pblock_tp_copies_by_kernel": (c_int, [c_void_p, c_void_p, c_void_p, POINTER(c_int)]),
         "pblock_tp_context_destroy": (None, [P]),
         "pblock_status_string": (ctypes.c_char_p, [c_int]),
         "pblock_last_error": (ctypes.c_char_p, []),
@@ -326,6 +327,14 @@ class TpContext:
         if self.handle:
             load_library().pblock_tp_context_destroy(self.handle)
             self.handle = None
+
+    def copies_by_kernel(self, src, dst) -> bool:
+        """Whether the pipelined calls copy src to dst with a kernel (this
+        process's own memory on this device) or with the DMA engines."""
+        out = c_int()
+        _check(load_library().pblock_tp_copies_by_kernel(self.handle, _ptr(src), _ptr(dst),
+                                                         ctypes.byref(out)))
+        return bool(out.value)
 
     def __enter__(self):
         return self
