@@ -7,10 +7,11 @@
 //     ahead and the barrier placed before the K-tile's last two phases (see
 //     the DMA kernel below); a build of its own (RK) for K that is no
 //     multiple of 64;
-//   - for operands whose tile offsets exceed 32 bits: MFMA
-//     v_mfma_f32_32x32x16_bf16, K-tile 64, double-buffered LDS, loads staged
-//     through registers with zero fill; an M- or N-contiguous operand is
-//     loaded as 8x8 blocks and transposed in registers on its way into LDS.
+//   - for operands whose tile offsets exceed 32 bits (rows of 4 million elements
+//     and more, where nothing is tuned): MFMA v_mfma_f32_32x32x16_bf16, K-tile
+//     64, double-buffered LDS, loads staged through registers with zero fill; an
+//     M- or N-contiguous operand is loaded as 8x8 blocks and transposed in
+//     registers on its way into LDS.
 // The MFMA is issued with the roles of the operands swapped (the N tile as
 // MFMA "A"), so each lane ends up holding four consecutive output columns of
 // one row.  The DMA kernel stages its accumulators through LDS before the
@@ -1141,10 +1142,14 @@ void gemm_dispatch(Dt dt, const void* A, int lda, const void* B, int ldb, int M,
   const int tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
   const size_t lds = 4 * (size_t)kTileBytes;  // both kernels: 128 KB
   static_assert(kStages * 2 * kDTile == 4 * kTileBytes, "DMA path LDS");
-  if (!dma_offsets_fit(AK, lda, BK, ldb)) {
-    gemm_bf16_kernel<AK, BK, EPI, GT><<<tiles, kThreads, lds, s>>>(
-        (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, ep);
-    return;
+  // Leading dimensions from 2^22 (K-contiguous) or 2^24 elements on.  The
+  // operands of BiasGelu are rows of the hidden size, at most 2^15.
+  if constexpr (EPI != Epi::BiasGelu) {
+    if (!dma_offsets_fit(AK, lda, BK, ldb)) {
+      gemm_bf16_kernel<AK, BK, EPI, GT><<<tiles, kThreads, lds, s>>>(
+          (const bf16*)A, lda, (const bf16*)B, ldb, M, N, K, ep);
+      return;
+    }
   }
   SplitPlan sp = gemm_split_plan(dt, M, N, K);
   if (sp.tail > 0 && (!split_ws || split_ws_floats < gemm_split_floats(dt, M, N, K)))
