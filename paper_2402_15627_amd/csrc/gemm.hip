@@ -1112,7 +1112,9 @@ double small_tile_us(int K, bool several) { return (several ? 2.0 : 0.5) + 5.7 *
 bool gemm_small_wins(int M, int N, int K) {
   const SplitPlan p = gemm_split_plan(Dt::BF16, M, N, K);
   const int nk = (K + kBK - 1) / kBK;
-  // (a single 256 x 256 tile, of at most four K-tiles, keeps its plan)
+  // A single 256 x 256 tile of at most four K-tiles keeps its plan, which
+  // pblock_gemm_plan has always reported for such a GEMM; not for speed (by the
+  // figures above 13 us, and 6 in 64 x 64 tiles).
   if (p.n_full == 1 && p.tail == 0) return false;
   double big = kTileUs + kStepUs * ((p.n_full + kCUs - 1) / kCUs) * nk;
   if (p.tail) {

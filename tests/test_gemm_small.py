@@ -1,8 +1,10 @@
 """The 64 x 64-tile bf16 GEMMs of small grids (K split over a workgroup's waves):
-where the plan takes them, and blocks whose GEMMs all run on them against the
-oracle, at tile edges, contractions that fill no slice of 32 or leave waves
-without one, ragged and whole token counts (separate and shared backward
-launches, db_in formed in both), both GeLU forms and every head dim."""
+where the plan takes them, and blocks on them against the oracle, at tile edges,
+contractions that fill no slice of 32 or leave waves without one, ragged and
+whole token counts (separate and shared backward launches, db_in formed in
+both), both GeLU forms and every head dim.  What of a block runs on other kernels
+is asserted too: a GEMM of one 256 x 256 tile and at most four K-tiles keeps that
+tile, and dh + dW_in with a long dh is cut along K instead."""
 import pytest
 
 from paper_2402_15627_amd import pblock as pb
@@ -15,8 +17,33 @@ SHAPES = [
     BlockShape("small_d96", 2, 127, 264, 2, 96, 72, 64, "bf16", gelu_tanh=False),
     BlockShape("small_pair", 2, 64, 320, 2, 64, 512, 40, "bf16"),
     BlockShape("small_pair_erf", 3, 64, 576, 3, 128, 1088, 192, "bf16", gelu_tanh=False),
+    BlockShape("small_pair_d96_erf", 3, 64, 320, 2, 96, 448, 192, "bf16", gelu_tanh=False),
     BlockShape("small_smoke", 1, 256, 512, 4, 128, 1024, 96, "bf16"),
 ]
+
+
+# the backward's pairs, and the GEMMs that keep one 256 x 256 tile
+PAIRS = {"small_pair": ("small", "small"), "small_pair_d96_erf": ("small", "small"),
+         "small_pair_erf": ("small", "split"), "small_smoke": ("small", "split")}
+
+
+def _plans(s):
+    for M, N, K in ((s.tokens, s.n_in, s.hidden), (s.tokens, s.hidden, s.k_out),
+                    (s.tokens, s.k_out, s.hidden), (s.hidden, s.k_out, s.tokens),
+                    (s.tokens, s.hidden, s.n_in), (s.n_in, s.hidden, s.tokens)):
+        yield M, N, K, pb.pblock_gemm_plan(pb.PB_BF16, M, N, K)
+
+
+@pytest.mark.parametrize("s", SHAPES, ids=[s.name for s in SHAPES])
+def test_blocks_take_small_tiles(s):
+    c = pb.config_from_shape(s)
+    kinds = tuple(k for k, _ in pb.pblock_backward_launches(c))
+    assert kinds == PAIRS.get(s.name, ("apart", "apart"))
+    for M, N, K, p in list(_plans(s))[:2 if s.name in PAIRS else 6]:
+        if M <= 256 and N <= 256 and K <= 256 and p.tiles == 1:
+            assert s.name == "small_one_token"
+        else:
+            assert p.tiles == -(-M // 64) * -(-N // 64), (M, N, K)
 
 
 @pytest.mark.parametrize("M,N,K,small", [
@@ -40,8 +67,6 @@ def test_small_blocks_match_oracle(s):
     print(f"[gpu] small GEMMs {s}", flush=True)
     c = pb.config_from_shape(s)
     assert pb.pblock_workspace_bytes(c, pb.WS_FORWARD) == 0  # no 256 x 256 tile is split
-    assert pb.pblock_backward_pairs(c) == ((True, True) if "pair" in s.name or "smoke" in s.name
-                                           else (False, False))
     inp = case(s, seed=3)
     errs, bad = compare(s, run_gpu(s, inp), run_oracle(s, inp))
     print("      " + ", ".join(f"{k}={v:.2e}" for k, v in errs.items()), flush=True)

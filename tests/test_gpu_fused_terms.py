@@ -8,13 +8,17 @@ rather than by launches of their own:
 
 Each is compared with the same sum over the block's own stored operands (the
 stash's O, the workspace's dO and dZ) in fp64: only fp32 summation order
-separates them (delta 1e-5 of max |delta|, db_in 1e-4 of max |db_in|).
-Shapes take the fused paths (bf16, every GEMM K a multiple of 64, heads of 64
-or 128 columns aligned to 128) with several batch rows (the epilogue maps a
-token row m to its batch row and position), and db_in is also checked against
-the fp64 oracle, as the block parity tests do.  A ragged token count, where
-the GEMMs run apart and separate launches form both terms, is checked the same
-way.
+separates them (delta 1e-5 of max |delta|, db_in 1e-4 of max |db_in|); db_in
+is also checked against the fp64 oracle, as the block parity tests do.
+
+delta is formed in the epilogue only by whole 256 x 256 tiles, with heads of 64 or
+128 columns aligned to 128; the "whole" shapes run with a workspace one byte
+short of the room for K-slices, so that both pairs launch whole.  They have
+several batch rows (the epilogue maps a token row m to its batch row and
+position), sequences that end inside a wave's 32 rows, ones of fewer than 32
+tokens, and tiles at the matrix edges.  The others form delta in its own launch:
+64 x 64 tiles, tiles cut along K, and a ragged token count, where the GEMMs run
+apart; all but the last form db_in in the shared launch.
 """
 import sys
 
@@ -29,8 +33,14 @@ pytestmark = pytest.mark.gpu
 SHAPES = [
     BlockShape("fused_d64_b2", 2, 320, 256, 4, 64, 512, 100, "bf16"),
     BlockShape("fused_d128_b3", 3, 128, 384, 2, 128, 640, 64, "bf16"),
+    BlockShape("whole_d64_b2", 2, 320, 1024, 4, 64, 2048, 100, "bf16"),
+    BlockShape("whole_d128_b3", 3, 128, 1024, 4, 128, 2048, 64, "bf16"),
+    BlockShape("whole_d64_erf_b4", 4, 112, 1344, 6, 64, 2880, 100, "bf16", gelu_tanh=False),
+    BlockShape("whole_d128_short_rows", 24, 16, 1024, 4, 128, 2048, 9, "bf16"),
+    BlockShape("split_d128_b3", 3, 128, 1024, 4, 128, 2048, 64, "bf16"),
     BlockShape("apart_ragged", 1, 333, 256, 2, 128, 512, 50, "bf16"),
 ]
+KINDS = {"fused": "small", "whole": "whole", "split": "split", "apart": "apart"}
 
 
 def _say(msg):
@@ -43,11 +53,12 @@ def test_delta_and_db_in_match_their_sums(s):
     import torch
     from paper_2402_15627_amd import pblock as pb
     _say(f"[gpu] fused backward terms {s.name}")
-    cfg = pb.config_from_shape(s)
-    fused = pb.pblock_backward_pairs(cfg) == (True, True)
-    assert fused == (s.name != "apart_ragged")
     inp = make_inputs(s, seed=3)
-    blk = pb.ParallelBlock(cfg, to_device(s, inp))
+    blk = pb.ParallelBlock(pb.config_from_shape(s), to_device(s, inp))
+    if s.name.startswith("whole"):
+        blk.ws = blk.ws[:-1]
+    kinds = [k for k, _ in pb.pblock_backward_launches(blk.cfg, ws_bytes=blk.ws.numel())]
+    assert kinds == 2 * [KINDS[s.name.split("_")[0]]], kinds
     blk.forward()
     blk.backward()
     torch.cuda.synchronize()

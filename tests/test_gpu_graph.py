@@ -27,15 +27,24 @@ def _say(msg):
     sys.stdout.flush()
 
 
-@pytest.mark.parametrize("block", ["parallel", "serial"])
-@pytest.mark.parametrize("s", SHAPES, ids=[s.name for s in SHAPES])
-def test_block_step_replays_in_a_graph(s, block):
+# "whole": a workspace one byte short of the room for K-slices, so that every
+# shared launch of the bf16 block is persistent
+CASES = [(s, block, room) for s in SHAPES for block in ("parallel", "serial")
+         for room in (("full", "whole") if s.dtype == "bf16" else ("full",))]
+
+
+@pytest.mark.parametrize("s,block,room", CASES, ids=[f"{s.name}-{b}-{r}" for s, b, r in CASES])
+def test_block_step_replays_in_a_graph(s, block, room):
     import torch
     from paper_2402_15627_amd import pblock as pb
     _say(f"[gpu] graph capture of forward + backward {s.name} {block}")
     cls = pb.ParallelBlock if block == "parallel" else pb.SerialBlock
     inp = make_inputs(s, seed=11, serial=block == "serial")
     blk = cls(pb.config_from_shape(s), to_device(s, inp))
+    if room == "whole":
+        blk.ws = blk.ws[:-1]
+        kinds = pb.pblock_backward_launches(blk.cfg, block, blk.ws.numel())
+        assert all(k == "whole" for k, _ in kinds), kinds
     outs = [blk.y] + list(blk.grads.values())
 
     def snapshot():
