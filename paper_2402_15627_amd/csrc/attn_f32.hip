@@ -49,6 +49,29 @@ struct F32Attn {
 };
 
 PB_DEV float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
+// Exponentials of scores in base 2.  In fp32 the products with log2 e lose up to
+// 2^-24 of a logit, an error of the probability itself where logits are large,
+// and a rounded scale log2 e in the forward alone would leave lse at another
+// temperature than the backward's; so what these roundings leave over is added
+// back.  dV against float64 with logits of 64 rms: 2 x 333 tokens, 16 heads of
+// 64 5.1e-6 -> 2.9e-6, 1024 tokens, 4 heads of 128 7.8e-6 -> 5.0e-6 (natural
+// exponentials of scores summed serially: 3.2e-6 and 6.0e-6); a block of 666
+// tokens, hidden 1024 579 us with and without, of 128 tokens 71.1 and 70.8.
+constexpr float kLog2eRest = 1.9259630e-8f;  // log2 e - kLog2e
+struct Base2 {
+  float c, rest;  // scale log2 e
+  PB_DEV Base2(float scale) {
+    c = scale * kLog2e;
+    rest = fmaf(scale, kLog2eRest, fmaf(scale, kLog2e, -c));
+  }
+  // 2^(score - ref), ref a base-2 reference, s finite
+  PB_DEV float exp(float s, float ref) const { return exp2_hw(fmaf(s, rest, fmaf(s, c, -ref))); }
+  // e^(score - L)
+  PB_DEV float prob(float s, float L) const {
+    const float L2 = L * kLog2e, left = fmaf(L, kLog2eRest, fmaf(L, kLog2e, -L2));
+    return exp2_hw(fmaf(s, rest, fmaf(s, c, -L2) - left));
+  }
+};
 PB_DEV f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 PB_DEV bool finite4(const f32x4& v) {
   // an infinity or NaN in any element makes the sum of v - v NaN
@@ -222,7 +245,7 @@ __global__ __launch_bounds__(64 * kAW) void attn_fwd_f32(F32Attn p, float* __res
   const int S = p.S, W = p.W, c0 = wi.head * D;
   const int q0 = ((int)gridDim.x - 1 - wi.bx) * kAR, q = q0 + i;
   const size_t tok0 = (size_t)wi.b * S;
-  const float c2 = p.scale * kLog2e;
+  const Base2 base(p.scale);
   f32x4 qf[D / 16], acc[D / 16];
   row_frag<D>(p.Q + (tok0 + min(q, S - 1)) * p.ld + c0, g, qf);
 #pragma unroll
@@ -242,10 +265,10 @@ __global__ __launch_bounds__(64 * kAW) void attn_fwd_f32(F32Attn p, float* __res
       const int key = k0 + 4 * g + e;
       s[e] = (unsigned)(q - key) < (unsigned)W && key < S ? s[e] : kNegInf;
     }
-    const float mt = max_groups(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))) * c2;
+    const float mt = max_groups(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))) * base.c;
     const float mn = fmaxf(m, mt), mu = mn == kNegInf ? 0.f : mn, a = exp2_hw(m - mu);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] = exp2_hw(fmaf(s[e], c2, -mu));
+    for (int e = 0; e < 4; ++e) s[e] = s[e] == kNegInf ? 0.f : base.exp(s[e], mu);
     l = l * a + ((s[0] + s[1]) + (s[2] + s[3]));
     m = mn;
 #pragma unroll
@@ -293,7 +316,8 @@ PB_DEV void dq_block(const F32Attn& p, const float* __restrict__ lse, float* __r
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int S = p.S, W = p.W, c0 = head * D, q = q0 + i, qc = min(q, S - 1);
   const size_t tok0 = (size_t)b * S, ro = ((size_t)b * p.H + head) * S;
-  const float c2 = p.scale * kLog2e, L = lse[ro + qc], L2 = L * kLog2e;
+  const Base2 base(p.scale);
+  const float L = lse[ro + qc];
   f32x4 qf[D / 16], gf[D / 16], dq[D / 16];
   row_frag<D>(p.Q + (tok0 + qc) * p.ld + c0, g, qf);
   row_frag<D>(p.dO + (tok0 + qc) * p.ld_do + c0, g, gf);
@@ -322,7 +346,7 @@ PB_DEV void dq_block(const F32Attn& p, const float* __restrict__ lse, float* __r
     for (int e = 0; e < 4; ++e) {
       const int key = k0 + 4 * g + e;
       const bool ok = (unsigned)(q - key) < (unsigned)W && key < S;
-      ds[e] = ok ? exp2_hw(fmaf(s[e], c2, -L2)) * (ds[e] - dl) : 0.f;
+      ds[e] = ok ? base.prob(s[e], L) * (ds[e] - dl) : 0.f;
     }
     add_rows<D>(kr, ds, dq);
   }
@@ -356,7 +380,7 @@ PB_DEV void dkdv_block(const F32Attn& p, const float* __restrict__ lse, float* _
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int S = p.S, W = p.W, c0 = head * D, key = j0 + i;
   const size_t tok0 = (size_t)b * S, ro = ((size_t)b * p.H + head) * S;
-  const float c2 = p.scale * kLog2e;
+  const Base2 base(p.scale);
   f32x4 kf[D / 16], vf[D / 16], dk[D / 16], dv[D / 16];
   const size_t own = (tok0 + min(key, S - 1)) * p.ld + c0;
   row_frag<D>(p.K + own, g, kf);
@@ -373,7 +397,7 @@ PB_DEV void dkdv_block(const F32Attn& p, const float* __restrict__ lse, float* _
     for (int s = 0; s < D / 16; ++s) t += qf[s] * gf[s];
     // row i's terms in every lane with l & 15 = i; a lane needs rows 4 g + e
     const float dli = sum_groups((t[0] + t[1]) + (t[2] + t[3]));
-    const float L2i = lse[ro + qi] * kLog2e;
+    const float Li = lse[ro + qi];
     row_frag<D>(p.Q + (tok0 + qi) * p.ld + c0, g, qf);
     const float *qr[4], *gr[4];
 #pragma unroll
@@ -388,8 +412,8 @@ PB_DEV void dkdv_block(const F32Attn& p, const float* __restrict__ lse, float* _
     for (int e = 0; e < 4; ++e) {
       const int q = q0 + 4 * g + e;
       const bool ok = (unsigned)(q - key) < (unsigned)W && q < S;
-      const float L2 = __shfl(L2i, 4 * g + e, 64), dl = __shfl(dli, 4 * g + e, 64);
-      pr[e] = ok ? exp2_hw(fmaf(pr[e], c2, -L2)) : 0.f;
+      const float L = __shfl(Li, 4 * g + e, 64), dl = __shfl(dli, 4 * g + e, 64);
+      pr[e] = ok ? base.prob(pr[e], L) : 0.f;
       ds[e] = ok ? pr[e] * (ds[e] - dl) : 0.f;
     }
     add_rows<D>(gr, pr, dv);

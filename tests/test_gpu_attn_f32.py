@@ -84,3 +84,26 @@ def test_non_finite_values_stay_in_their_window(bad):
     # the infinity itself is kept where the definition gives one
     if np.isinf(bad):
         assert (got["o"][0, 40:60, 7] == bad).all()
+
+
+def test_large_logits():
+    """Logits of 64 rms, lse around 150: lse itself is rounded to 2^-17 there, rms
+    4.4e-6 of every probability that the backward forms from it, so dV, a sum
+    of probabilities times dO, may be 4e-6 off; products with log2 e rounded on
+    top (half a unit in the last place of 216, twice) would take it to 5e-6."""
+    B, S, nh, d, W = 1, 333, 12, 64, 150
+    print("[gpu] fp32 attention, large logits", flush=True)
+    rng = np.random.default_rng(8)
+    q, k, v, do = (normal(rng, B, S, nh * d) for _ in range(4))
+    q *= 8
+    k *= 8
+    got = run(B, S, nh, d, W, q, k, v, do)
+    diff, size = 0.0, 0.0
+    for h in range(nh):
+        sl = slice(h * d, (h + 1) * d)
+        a = [t[0, :, sl].astype(np.float64) for t in (q, k, v, do)]
+        dv = orc.swa_head_backward(*a, W)[2]
+        diff += np.square(got["dv"][0, :, sl] - dv).sum()
+        size += np.square(dv).sum()
+    print(f"      dV {np.sqrt(diff / size):.2e}", flush=True)
+    assert np.sqrt(diff / size) <= 4e-6
