@@ -567,16 +567,6 @@ PB_DEV void wave_epilogue_lds(const EpiArgs& ep, float* __restrict__ part_tile,
 // One work item of the DMA GEMM: K-tiles [kt0, kt1) of output tile lid
 // (slice >= 0: one K-slice of tail tile lid, whose fp32 partial tile goes to
 // part for splitk_reduce).
-// Sum of a fragment's eight bf16 values, added to acc in fp32.
-PB_DEV float sum_bf16x8(const bf16x8& p, float acc) {
-  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-  const bf16x2_t one = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-  for (int i = 0; i < 8; i += 2)
-    acc = __builtin_amdgcn_fdot2_f32_bf16(bf16x2_t{p[i], p[i + 1]}, one, acc, false);
-  return acc;
-}
-
 // RS (StoreF32 only): also the row sums of A over this work item's K-tiles,
 // rowsum[m] = sum_k A(m, k), from the A fragments the MFMAs consume (the
 // caller sets RS for the tiles of the first tile column only).

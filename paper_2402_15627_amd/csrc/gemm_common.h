@@ -1,5 +1,5 @@
-// Device code shared by the bf16 and fp32 projection GEMMs: the epilogues of
-// four consecutive output columns and the order in which tiles are walked.
+// Device code shared by the projection GEMMs: the epilogues of four consecutive
+// output columns, a fragment's row sum and the order in which tiles are walked.
 #pragma once
 
 #include "common.h"
@@ -65,6 +65,16 @@ PB_DEV void ln_terms4(const EpiArgs& ep, int m, int n, const float* v, float mu,
     s1 += g;
     s2 += g * ((xv[e] - mu) * rs);
   }
+}
+
+// Sum of a fragment's eight bf16 values, added to acc in fp32.
+PB_DEV float sum_bf16x8(const bf16x8& p, float acc) {
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  const bf16x2_t one = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+  for (int i = 0; i < 8; i += 2)
+    acc = __builtin_amdgcn_fdot2_f32_bf16(bf16x2_t{p[i], p[i + 1]}, one, acc, false);
+  return acc;
 }
 
 // Tile order.  Workgroup b runs on XCD b % 8; xcd_remap gives each XCD a

@@ -109,15 +109,6 @@ struct Side {
   }
 };
 
-PB_DEV float sum8(const bf16x8& p, float acc) {
-  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-  const bf16x2_t one = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-  for (int i = 0; i < 8; i += 2)
-    acc = __builtin_amdgcn_fdot2_f32_bf16(bf16x2_t{p[i], p[i + 1]}, one, acc, false);
-  return acc;
-}
-
 struct SmallGemm {
   const bf16* A;
   int lda;
@@ -167,7 +158,7 @@ PB_DEV void small_tile(const SmallGemm& G, int lid, unsigned char* __restrict__ 
     if constexpr (EPI == Epi::StoreF32) {
       if (rows) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rsum[i] = sum8(fa[i], rsum[i]);
+        for (int i = 0; i < 4; ++i) rsum[i] = sum_bf16x8(fa[i], rsum[i]);
       }
     }
 #pragma unroll
