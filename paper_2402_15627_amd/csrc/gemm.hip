@@ -1277,7 +1277,9 @@ static double delta_us(const GemmSpec& g) {
 // and cutting the first GEMM only delays them.  Chosen on the two pairs of 140
 // blocks of 64 to 8192 tokens, each timed whole and with 2 to 16 slices: what it
 // picks is nowhere slower than whole tiles (0.2% at most), and slower than the
-// best of all by 1% on average and by 10 to 12% in three pairs.
+// best of all by 1% on average and by 10 to 12% in three pairs.  Of 52 other
+// backward calls with a cut pair, one is slower than without room for slices (3%:
+// 3264 tokens, hidden 1792, A 896, FFN 3584, an estimate of 104 steps against 105).
 // Measured, the pair whole -> cut: dh + dW_in at 512 tokens, hidden 2048, A 1024,
 // FFN 8192 205 -> 67 us; 1024, 4096, 2048, 16384 530 -> 337; 192, 8320, 8320,
 // 33280 1458 -> 656.  Left whole: dC + dW_out at 7296 tokens, hidden 2176, A 256,
